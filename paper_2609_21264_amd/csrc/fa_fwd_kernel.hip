@@ -119,6 +119,32 @@ __device__ __forceinline__ void q_ready(bf16x8& r) {
     asm volatile("" : "+v"(r));
 }
 
+// Slot of a tile in a ring of N slots of STEP bytes. A ring of 2 or 4 slots takes the low bits of the
+// tile index. For 3 slots the remainder would cost a multiply-high chain in front of each step's first
+// LDS reads, so the offset is carried from tile to tile instead (next()): one add, compare and select,
+// in inline assembly so that they stay scalar: the loads' LDS base (M0) must be a scalar, and a select
+// that also feeds vector addresses is selected as a vector instruction. Measured (interleaved, one
+// box): H4 777 x 3001 d128 28.5 -> 26.7 us, one head S16384 d128 153.9 -> 145.2 us, B2 28/4 777 x 5001
+// 119.5 -> 114.3 us; carrying the power-of-two rings too cost B8 H12 S512 d64 2.5 %, so they are not.
+template <int STEP, int N>
+struct Ring {
+  static constexpr bool kCarried = (N & (N - 1)) != 0;
+  int off;  // carried offset
+  __device__ __forceinline__ explicit Ring(int tile) : off(tile % N * STEP) {}
+  __device__ __forceinline__ void next() {
+    if constexpr (kCarried)
+      asm("s_add_u32 %0, %0, %1\n\ts_cmp_eq_u32 %0, %2\n\ts_cselect_b32 %0, 0, %0"
+          : "+s"(off)
+          : "i"(STEP), "i"(STEP * N)
+          : "scc");
+  }
+  // Offset of tile `t`, which is the tile the carried offset stands at.
+  __device__ __forceinline__ int at(int t) const {
+    if constexpr (kCarried) return off;
+    return (int)((unsigned)t % N) * STEP;
+  }
+};
+
 // Compile-time configuration of one kernel instance: head dimensions, key-tile width, waves per
 // workgroup, 32-row query blocks per wave, causal masking, split mode, workgroups sharing a CU (OCC),
 // K and V fragments read ahead from LDS (KPF, VPF), K and V ring slots in LDS (NKR, NVR), and the
@@ -600,10 +626,9 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
   // (tile indices are never negative: unsigned remainders, a mask for the power-of-two ring sizes)
   auto kslot = [&](int t) { return smem + ((unsigned)t % C::NKR) * C::K_BYTES; };
   auto vslot = [&](int t) { return smem + C::NKR * C::K_BYTES + ((unsigned)t % C::NVR) * C::V_BYTES; };
-  // This wave's keys of tile t (rows kpart .. kpart + WBN - 1 of the slot). The K and V swizzles
+  // This wave's keys of K tile t (rows kpart .. kpart + WBN - 1 of the slot). The K and V swizzles
   // repeat every 32 rows, so a part starting at row 32 reads like a tile of its own.
   auto kmine = [&](int t) { return kslot(t) + kpart * (DQK * 2); };
-  auto vmine = [&](int t) { return vslot(t) + kpart * (DV * 2); };
 #pragma unroll
   for (int g = -C::KA; g < 0; ++g) {
     kload.issue(kb0 + (g + C::KA) * BN, kslot(g + C::KA), wave);
@@ -658,15 +683,26 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
   int krem, vrem;
   u32x4 gk = kload.rsrc_walk(kb0 + (C::KA - 1) * BN, krem), gv = vload.rsrc_walk(kb0 + (C::VA - 1) * BN, vrem);
   uint32_t gkl = 0, gvl = 0;
+  // The rings at the start of step j: K(j+KA) overwrites the slot of K(j) and V(j+VA) that of V(j-2);
+  // moved on by one tile they stand at K(j+1) and V(j-1), which the step reads.
+  unsigned char* const vring = smem + C::NKR * C::K_BYTES;
+  Ring<C::K_BYTES, C::NKR> kring(0);
+  Ring<C::V_BYTES, C::NVR> vpos(C::NVR - 2);
+  auto kread = [&](int t) { return smem + kring.at(t) + kpart * (DQK * 2); };
+  auto vread = [&](int t) { return vring + vpos.at(t) + kpart * (DV * 2); };
   auto sync_step = [&](int j) {
     wait_vmcnt<C::V_LOADS + (C::KA - 2) * (C::K_LOADS + C::V_LOADS)>();
     compiler_fence();
     __builtin_amdgcn_s_barrier();
     compiler_fence();
     kload.advance(gk, krem);
-    gkl = kload.lds(kslot(j + C::KA), wave);
+    gkl = kload.lds(smem + kring.at(j + C::KA), wave);
     vload.advance(gv, vrem);
-    gvl = vload.lds(vslot(j + C::VA), wave);
+    gvl = vload.lds(vring + vpos.at(j + C::VA), wave);
+    if constexpr (decltype(kring)::kCarried) gkl = __builtin_amdgcn_readfirstlane(gkl);
+    if constexpr (decltype(vpos)::kCarried) gvl = __builtin_amdgcn_readfirstlane(gvl);
+    kring.next();
+    vpos.next();
   };
   auto issue = [&](int k) {
     if (k < C::K_LOADS)
@@ -681,14 +717,14 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
   int j = 0;
   for (; j + 1 < nt; j += 2) {
     sync_step(j);
-    st.step(sA, sB, pA, pB, kmine(j + 1), j > 0 ? vmine(j - 1) : kmine(1), j >= n_plain,
+    st.step(sA, sB, pA, pB, kread(j + 1), j > 0 ? vread(j - 1) : kmine(1), j >= n_plain,
             kb0 + j * BN + kpart, issue);
     sync_step(j + 1);
-    st.step(sB, sA, pB, pA, kmine(j + 2), vmine(j), j + 1 >= n_plain, kb0 + (j + 1) * BN + kpart, issue);
+    st.step(sB, sA, pB, pA, kread(j + 2), vread(j), j + 1 >= n_plain, kb0 + (j + 1) * BN + kpart, issue);
   }
   if (j < nt) {
     sync_step(j);
-    st.step(sA, sB, pA, pB, kmine(j + 1), j > 0 ? vmine(j - 1) : kmine(1), j >= n_plain,
+    st.step(sA, sB, pA, pB, kread(j + 1), j > 0 ? vread(j - 1) : kmine(1), j >= n_plain,
             kb0 + j * BN + kpart, issue);
   }
   if (nt > 0) {
@@ -709,7 +745,8 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
       for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int r = 0; r < 8; ++r) pl[kb][qb][r] = (pA[kb][qb][r] & take_a) | (pB[kb][qb][r] & ~take_a);
-    st.pv_tile(pl, vmine(nt - 1));
+    vpos.next();
+    st.pv_tile(pl, vread(nt - 1));
   }
 
   // No load may still be writing this workgroup's LDS when it exits (the prologue issues loads even
