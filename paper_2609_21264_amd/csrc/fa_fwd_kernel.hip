@@ -176,19 +176,27 @@ struct Cfg {
   // both were last read in step j-1, which every wave has finished at the barrier of step j.
   static constexpr int NKR = NKR_, NVR = NVR_;
   static constexpr int KA = NKR, VA = NVR - 2;  // how far ahead step j loads K and V tiles
-  static constexpr int LDS_BYTES = NKR * K_BYTES + NVR * V_BYTES;
+  static constexpr int RING_BYTES = NKR * K_BYTES + NVR * V_BYTES;
+  // The rings' LDS also stages the output tile (STAGE_BYTES) and, behind it, the exchange of the key
+  // parts' results (XCH_BYTES: per lane of every row chunk, O of all parts but one and every part's
+  // reference maximum and row sum); with small key tiles these are the larger.
+  static constexpr int STAGE_BYTES = RWAVES * 32 * QB * DV * 2;
+  static constexpr int XCH_BYTES =
+      KSPLIT > 1 ? RWAVES * ((KSPLIT - 1) * (DV / 2) + KSPLIT * 2) * QB * 64 * 4 : 0;
+  static constexpr int LDS_BYTES =
+      RING_BYTES > STAGE_BYTES + XCH_BYTES ? RING_BYTES : STAGE_BYTES + XCH_BYTES;
   // Direct-to-LDS loads per wave per tile (each moves 64 lanes x 16 bytes).
   static constexpr int K_LOADS = BN * KCH / 64 / NWAVES;
   static constexpr int V_LOADS = BN * VCH / 64 / NWAVES;
   static_assert(DQK % 32 == 0 && DV % 64 == 0, "head dims: d_qk multiple of 32, d_v multiple of 64");
-  static_assert(BN % 64 == 0, "key tiles of whole 64-key units");
+  static_assert(WBN % 32 == 0, "every wave takes whole 32-key blocks of a tile");
   static_assert((BN * KCH) % (64 * NWAVES) == 0 && (BN * VCH) % (64 * NWAVES) == 0, "tile split over waves");
   // KA - 1 <= VA <= KA: V(j-1) is issued before K(j+1) (so one counted wait covers both), and the
   // prologue's groups j = -KA .. -1 hold every tile's first load.
   static_assert(NKR >= 2 && NKR + 1 <= NVR && NVR <= NKR + 2, "ring sizes");
   static_assert(KA * (K_LOADS + V_LOADS) < 64 && VA * (K_LOADS + V_LOADS) < 64, "vmcnt range");
   static_assert(LDS_BYTES * OCC_ <= 163840, "LDS budget of the workgroups sharing a CU");
-  static_assert(KSPLIT == 1 || (KSPLIT == 2 && !SPLIT && NWAVES % 2 == 0), "key halves: two wave sets, not split mode");
+  static_assert(KSPLIT == 1 || (!SPLIT && NWAVES % KSPLIT == 0), "key parts: equal wave sets, not split mode");
 };
 
 // Division by a divisor that is fixed for the launch, as a multiply-high and two shifts (Granlund and
@@ -762,56 +770,100 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
   compiler_fence();
 
   if constexpr (C::KSPLIT > 1) {
-    // Merge of the two key halves (the combination step of Alg. 2 inside the workgroup): the second
-    // wave set hands its O, reference maxima and lane row sums to the wave of the first set with the
-    // same rows through LDS, lane by lane (both hold the same rows and dims in the same registers),
-    // and exits. With m = max(m_a, m_b): O = O_a 2^(m_a - m) + O_b 2^(m_b - m), likewise l; a half
-    // that saw no visible key (m = -inf, O = 0, l = 0) gets weight 0. The exchange area lies past
-    // the first set's output staging tiles.
-    constexpr int NF = A::DB * QB * 16;  // O floats per lane
-    constexpr int XCH_OFF = C::RWAVES * 32 * QB * DV * 2;
-    static_assert(XCH_OFF + C::RWAVES * (NF + 2 * QB) * 64 * 4 <= C::LDS_BYTES, "exchange area fits the LDS");
-    float* xch = reinterpret_cast<float*>(smem + XCH_OFF) + rwave * (NF + 2 * QB) * 64;
-    if (kset == 1) {
+    // Merge of the key parts (the combination step of Alg. 2 inside the workgroup). The waves with the
+    // same rows, one per set, hold the same rows and dims in the same registers. Each set finishes a
+    // share of them: the accumulators of a wave are NCH chunks of 4 registers, set t owns chunks
+    // [t * CPS, (t + 1) * CPS), and every wave hands the chunks it does not own, with its reference
+    // maxima and lane row sums, to their owners through LDS, lane by lane. With m the maximum of the
+    // parts' references m_k: O = sum O_k 2^(m_k - m), likewise l, added in the order of the parts; a part
+    // that saw no visible key (m_k = -inf, O = 0, l = 0) gets weight 0. The output tile is staged like
+    // below, and each set stores its share of its rows. The exchange area lies past the staging tiles.
+    // (One set merging everything while the others exit took 0.1-0.4 us more per workgroup.)
+    constexpr int KP = C::KSPLIT, NCH = A::DB * QB * 4, CPS = NCH / KP;
+    static_assert(NCH % KP == 0, "accumulator chunks split over the sets");
+    constexpr int WSTR = (KP - 1) * NCH * 256 + KP * 2 * QB * 64;  // exchanged floats per row chunk
+    static_assert(C::STAGE_BYTES + C::RWAVES * WSTR * 4 <= C::LDS_BYTES, "exchange area fits the LDS");
+    float* const xo = reinterpret_cast<float*>(smem + C::STAGE_BYTES) + rwave * WSTR;
+    float* const xml = xo + (KP - 1) * NCH * 256;
+    // Chunk c of its owner t, as handed over by part k != t.
+    auto xchunk = [&](int t, int k, int c) {
+      return reinterpret_cast<f32x4*>(xo + (((t * (KP - 1) + (k < t ? k : k - 1)) * CPS + c % CPS) * 64 + lane) * 4);
+    };
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
+    for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-        for (int db = 0; db < A::DB; ++db) {
-          agpr_fence<A::AG>(st.oacc[db][qb]);
+      for (int db = 0; db < A::DB; ++db) agpr_fence<A::AG>(st.oacc[db][qb]);
 #pragma unroll
-          for (int g4 = 0; g4 < 4; ++g4) {
-            const f32x16& o = st.oacc[db][qb];
-            *reinterpret_cast<f32x4*>(xch + (((qb * A::DB + db) * 4 + g4) * 64 + lane) * 4) =
-                f32x4{o[4 * g4], o[4 * g4 + 1], o[4 * g4 + 2], o[4 * g4 + 3]};
-          }
+    for (int t = 0; t < KP; ++t)
+      if (kset != t)
+#pragma unroll
+        for (int c = t * CPS; c < (t + 1) * CPS; ++c) {
+          const f32x16& o = st.oacc[(c / 4) % A::DB][c / (4 * A::DB)];
+          const int g4 = c % 4;
+          *xchunk(t, kset, c) = f32x4{o[4 * g4], o[4 * g4 + 1], o[4 * g4 + 2], o[4 * g4 + 3]};
         }
-        xch[NF * 64 + qb * 64 + lane] = st.m_run[qb];
-        xch[NF * 64 + (QB + qb) * 64 + lane] = st.l_run[qb];
-      }
-    }
-    compiler_fence();
-    __builtin_amdgcn_s_barrier();
-    compiler_fence();
-    if (kset == 1) return;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      const float m_b = xch[NF * 64 + qb * 64 + lane], l_b = xch[NF * 64 + (QB + qb) * 64 + lane];
-      const float m_a = st.m_run[qb], m = fmaxf(m_a, m_b);
-      const float wa = m_a == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_a - m);
-      const float wb = m_b == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_b - m);
-      st.m_run[qb] = m;
-      st.l_run[qb] = st.l_run[qb] * wa + l_b * wb;
-#pragma unroll
-      for (int db = 0; db < A::DB; ++db) {
-        agpr_fence<A::AG>(st.oacc[db][qb]);
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const f32x4 ob = *reinterpret_cast<const f32x4*>(xch + (((qb * A::DB + db) * 4 + g4) * 64 + lane) * 4);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) st.oacc[db][qb][4 * g4 + e] = st.oacc[db][qb][4 * g4 + e] * wa + ob[e] * wb;
-        }
-      }
+      xml[(kset * 2 * QB + qb) * 64 + lane] = st.m_run[qb];
+      xml[(kset * 2 * QB + QB + qb) * 64 + lane] = st.l_run[qb];
     }
+    __syncthreads();  // with the wait for this wave's LDS writes
+    constexpr int RB = DV * 2, WROWS = 32 * QB;
+    unsigned char* const tile = smem + rwave * WROWS * RB;
+    const int osw = o_swizzle<DV>(st.i32) << 4, ohalf = (st.h ^ o_half<DV>(st.i32)) << 3;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      float w[KP], l = 0.f, m = -INFINITY;
+#pragma unroll
+      for (int k = 0; k < KP; ++k) {
+        w[k] = xml[(k * 2 * QB + qb) * 64 + lane];
+        m = fmaxf(m, w[k]);
+      }
+#pragma unroll
+      for (int k = 0; k < KP; ++k) {
+        w[k] = w[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(w[k] - m);
+        l += xml[(k * 2 * QB + QB + qb) * 64 + lane] * w[k];
+      }
+      const float l_tot = half_swap_sum(l);
+      const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+      unsigned char* const srow = tile + (qb * 32 + st.i32) * RB + ohalf;
+#pragma unroll
+      for (int t = 0; t < KP; ++t)
+        if (kset == t)
+#pragma unroll
+          for (int c = t * CPS; c < (t + 1) * CPS; ++c) {
+            if (c / (4 * A::DB) != qb) continue;
+            const f32x16& own = st.oacc[(c / 4) % A::DB][qb];
+            f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < KP; ++k) {
+              const int g4 = c % 4;
+              const f32x4 ok = k == t ? f32x4{own[4 * g4], own[4 * g4 + 1], own[4 * g4 + 2], own[4 * g4 + 3]}
+                                      : *xchunk(t, k, c);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[e] = k == 0 ? ok[e] * w[k] : o[e] + ok[e] * w[k];
+            }
+            *reinterpret_cast<uint2*>(srow + (((c % (4 * A::DB)) << 4) ^ osw)) =
+                make_uint2(pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv));
+          }
+      const int row = st.qw + qb * 32 + st.i32;
+      if (p.lse != nullptr && kset == 0 && st.h == 0 && row < p.sq)
+        p.lse[(size_t)(b * p.hq + hq) * p.sq + row] = l_tot > 0.f ? (m + log2f(l_tot)) * kLn2 : -INFINITY;
+    }
+    __syncthreads();
+    constexpr int CPR = RB / 16, RPI = 64 / CPR, NIT = WROWS / RPI / KP;
+    static_assert(NIT >= 1, "rows split over the sets");
+    uint16_t* const ohead = p.o + (size_t)(b * p.hq + hq) * p.sq * DV;
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      const int r = (kset * NIT + it) * RPI + lane / CPR, c = lane % CPR, row = st.qw + r;
+      const unsigned char* chunk = tile + r * RB + ((c ^ o_swizzle<DV>(r)) << 4);
+      const int hl = o_half<DV>(r) << 3;
+      const uint2 x = *reinterpret_cast<const uint2*>(chunk + hl);
+      const uint2 y = *reinterpret_cast<const uint2*>(chunk + (hl ^ 8));
+      if (row < p.sq) *reinterpret_cast<u32x4*>(ohead + (size_t)row * DV + c * 8) = u32x4{x.x, x.y, y.x, y.y};
+    }
+    return;
   }
 
   // ---- epilogue: O = acc / l, LSE = ln 2 * (m + log2 l) ---------------------------------------
@@ -846,7 +898,7 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
     // straight from the accumulator layout, every instruction would touch 32 rows 16 bytes at a time.
     constexpr int RB = DV * 2;           // bytes per output row
     constexpr int WROWS = 32 * QB;       // rows per wave
-    static_assert(C::NWAVES * WROWS * RB <= C::LDS_BYTES, "output staging fits in the ring slots");
+    static_assert(C::RWAVES * WROWS * RB <= C::LDS_BYTES, "output staging fits in the ring slots");
     unsigned char* stage = smem + wave * WROWS * RB;
   #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
@@ -976,6 +1028,19 @@ void fa_fwd_kernel_preload(const uint16_t* a_q, int a_sq, int a_sk, int a_hq, in
 template <int DQK, int DV, bool CAUSAL, bool SPLIT = false>
 struct Instance {
   using C = Cfg<DQK, DV, FA_BN, FA_NWAVES, FA_QB, CAUSAL, SPLIT, 1, FA_KPF, FA_VPF, FA_NKR, FA_NVR>;
+};
+// The long instance at d = 64: the same 256-row blocks in 32-key tiles, two workgroups per CU. At d = 64
+// every MFMA comes with 9 full-rate-equivalent VALU instructions of softmax (36 cycles against its own
+// 32), which one wave per SIMD serialises behind it (measured 49 cycles a slot against 44 with two
+// waves). A wave's 64 rows with 32 keys need O 64, Q 32, two score tiles 64 and P 32 registers, so two
+// waves per SIMD fit (218 VGPRs, no AGPR) and every K and V fragment still feeds two MFMAs. Measured
+// against 64-key tiles with one wave per SIMD (interleaved, one box): GQA 14/2 S32768 causal 1892 ->
+// 1782 us, H16 S32768 causal 2103 -> 1978, B8 H12 S4096 412 -> 380, B8 H16 S3000 causal 192 -> 167. A
+// third K slot cost 5 %, reading K fragments 1 ahead 1.5 %, key halves on 64-key tiles 2-6 %. Split mode
+// keeps the 64-key tiles: its grids of about one workgroup per CU measured 0.74-1.08x with these.
+template <bool CAUSAL>
+struct Instance<64, 64, CAUSAL, false> {
+  using C = Cfg<64, 64, 32, 4, 2, CAUSAL, false, 2, 2, 4, 2, 4>;
 };
 template <int DQK, int DV, bool CAUSAL>
 struct ShortInstance {
