@@ -281,14 +281,16 @@ const char* fa_status_str(fa_status_t s);
  * these rows each. Host arithmetic only. */
 int fa_block_rows(int d_qk, int d_v, int causal);
 
-/* Query rows per workgroup holding one query head of the fused-kernel instance that fa_fwd and
+/* Query rows per block holding one query head of the fused-kernel instance that fa_fwd and
  * fa_fwd_ex (without split mode) launch for a problem of B batches, Hq query heads and Sq query rows:
- * 256 (long instance: one workgroup per compute unit), 128 (short instance: two per compute unit, at
- * most 1024 blocks at d = 64 and 256 at d = 128, i.e. blocks of the long instance's rows) or 64 (key
- * halves: each half of a workgroup's waves takes one half of every key tile, and the halves are
- * merged at the end; causal problems of at most 320 blocks at d = 64 and 192 at d = 128, others of at
- * most 64 and 128). Every instance computes the same function (Eq. (1) by Alg. 1); which one runs
- * follows from the grid size alone. 0 for unsupported head dimensions or negative sizes. Host
+ * 256 (long instance: one workgroup per compute unit, two at d = 64), 128 (short instance: two per
+ * compute unit, at most 1024 blocks at d = 64 and 256 at d = 128, i.e. blocks of the long instance's
+ * rows) or 64 (key parts: the wave sets of a workgroup take the parts of every key tile and merge their
+ * results at the end; causal problems of at most 320 blocks at d = 64 and 192 at d = 128, others of at
+ * most 64 and 128). The key-parts blocks run as one workgroup each (two halves of 64-key tiles) or, on
+ * grids that would leave compute units idle, as two workgroups of 32 rows (four quarters of 128-key
+ * tiles). Every instance computes the same function (Eq. (1) by Alg. 1); which one runs
+ * follows from the sizes alone. 0 for unsupported head dimensions or negative sizes. Host
  * arithmetic only. */
 int fa_fwd_rows(int B, int Hq, int Sq, int d_qk, int d_v, int causal);
 

@@ -1069,6 +1069,34 @@ struct HalfInstance {
   using C = Cfg<DQK, DV, 64, 4, 1, CAUSAL, false, DQK >= 128 ? 2 : 3, 2, DQK >= 128 ? 2 : 4, 2, DQK >= 128 ? 3 : 4, 2>;
 };
 
+// Key quarters: the 4 waves share 32 query rows and each takes one 32-key quarter of every 128-key tile
+// (the merge takes the four parts' results). Half the steps of the key halves at the same work per wave
+// and step, but every workgroup reads each K/V tile for 32 rows only, so it is for grids that leave CUs
+// idle, where nothing but the length of a chain counts: there a step takes 350-600 ns whatever it
+// computes (waits, barrier, LDS and MFMA latency with one wave per SIMD). Two workgroups per CU at
+// d = 64 (80 KiB of LDS), one at d = 128 (160 KiB).
+template <int DQK, int DV, bool CAUSAL>
+struct QuarterInstance {
+  using C = Cfg<DQK, DV, 128, 4, 1, CAUSAL, false, DQK >= 128 ? 1 : 2, 2, DQK >= 128 ? 2 : 4, 2, 3, 4>;
+};
+
+// Whether a problem of the key-halves instance runs the quarters: its 32-row workgroups are at most one
+// per CU. Measured against the halves (interleaved, one box): d = 64 one head S256 5.15 -> 4.62 us, H12
+// S512 causal 6.48 -> 5.37, H8 S1024 9.1 -> 6.8, 16/2 100 x 16384 97 -> 57; d = 128 H8 S1024 12.3 -> 10.6,
+// 4 heads 333 x 999 12.1 -> 9.8, 16/2 100 x 16384 142 -> 83; at 320 workgroups 0.68-0.95x at d = 128
+// and level at d = 64. Twice as many where the causal triangle makes the second half of the grid short
+// (at least half as many rows as keys): d = 64 H16 S1024 9.3 -> 7.6, H4 S4096 26.3 -> 19.4 (at 640 0.85x
+// at S1024); d = 128 from 2048 keys on, H8 S2048 level, H4 S4096 35.4 -> 30.4, one head S16384 145 -> 98
+// (512 workgroups at S1024 0.83x). Up to 64 keys at d = 64 (0.92x) and 256 at d = 128 (0.85-1.00x) the
+// four-way merge costs more than the one or two steps saved.
+bool key_quarters(const FwdParams& p, int d_qk, bool causal) {
+  constexpr int64_t kCus = 256;
+  const int64_t wgs = (int64_t)p.batch * p.hq * ((p.sq + 31) / 32);
+  const bool triangle = causal && (int64_t)p.sq * 2 >= p.sk;
+  if (d_qk == 64) return p.sk > 64 && wgs <= (triangle ? 2 * kCus : kCus);
+  return p.sk > 256 && wgs <= (triangle && p.sk >= 2048 ? 2 * kCus : kCus);
+}
+
 // Largest grid of long-instance blocks (256 row-heads) that runs the short instance instead. At
 // d = 128 the CU count of MI355X, where the long instance would leave CUs idle. At d = 64, where a
 // step carries twice the softmax work per MFMA and the long instance's one wave per SIMD exposes it,
@@ -1132,7 +1160,10 @@ hipError_t launch_cfg(FwdParams p, hipStream_t stream) {
 template <int DQK, int DV, bool CAUSAL, bool SPLIT>
 hipError_t launch_instance(FwdParams p, Kind kind, hipStream_t stream) {
   if constexpr (!SPLIT && DQK != 192) {
-    if (kind == Kind::kHalf) return launch_cfg<typename HalfInstance<DQK, DV, CAUSAL>::C>(p, stream);
+    if (kind == Kind::kHalf) {
+      if (key_quarters(p, DQK, CAUSAL)) return launch_cfg<typename QuarterInstance<DQK, DV, CAUSAL>::C>(p, stream);
+      return launch_cfg<typename HalfInstance<DQK, DV, CAUSAL>::C>(p, stream);
+    }
   }
   if constexpr (!SPLIT && DQK != 192) {
     if (kind == Kind::kShort) {
