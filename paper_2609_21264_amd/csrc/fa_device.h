@@ -19,6 +19,7 @@ typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
 constexpr int kNumXcd = 8;
+constexpr int kCusPerXcd = 32;
 
 // Row order of a 32-key block in the score product's A operand: A-row i holds key perm32(i).
 // With the 32x32 accumulator layout (register r of a lane in half h holds A-row

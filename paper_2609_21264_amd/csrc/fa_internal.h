@@ -24,6 +24,7 @@ struct FwdParams {
   // Work decomposition constants (host-computed): the items in whole spans of 8 groups, and the
   // multiply-high constants for dividing by group, hkv and batch, their shifts packed 6 bits apart.
   int full;
+  int head_chunk, head_chunked;  // key/value heads per chunk, and how many of them run in whole chunks
   uint32_t m_group, m_hkv, m_batch, shifts;
   // Split mode only: number of key-range parts, and the partial results, in the caller's workspace:
   // o_part fp32 [n_split][B][Hq][Sq][d_v] (O of each part normalised by its own row sum), lse_part

@@ -60,3 +60,24 @@ def test_key_parts_match_oracle(w, spiked):
     # spiked or sigma = 2: the bar derived from the bf16 rounding of P and O
     compare(to_f64(o), lse.cpu().double().numpy(), o_ref, lse_ref, w.name, max(1.0, w.sigma),
             o_bar=rounding_bar(vf, w.Hq) if spiked or w.sigma > 1.0 else None)
+
+
+# At least four chunks of key/value heads (long instance): the work order visits every (head, query
+# block) once whatever the heads left after the whole chunks, the group size and the batch.
+CHUNKED = [
+    _w("chunks", 128, 37, 37, 8200, 40, False),
+    _w("chunks gqa8", 128, 264, 33, 2100, 120, True),
+    _w("chunks gqa7", 128, 231, 33, 2400, 300, True),
+    _w("chunks", 64, 67, 67, 8200, 33, False),
+    W.small("chunks 192/128", B=3, Hq=23, Hkv=23, Sq=8200, Sk=260, dqk=192, dv=128, causal=True, seed=633),
+]
+
+
+@pytest.mark.parametrize("w", CHUNKED, ids=[w.name for w in CHUNKED])
+def test_head_chunks_match_oracle(w):
+    assert fa.fa_fwd_rows(w.B, w.Hq, w.Sq, w.dqk, w.dv, w.causal) == 256
+    q, k, v = W.make_inputs(w)
+    print(f"\n[case] {w}", flush=True)
+    o, lse = run_gpu(q, k, v, w)
+    o_ref, lse_ref = naive_attention(to_f64(q), to_f64(k), to_f64(v), w.scale, w.causal)
+    compare(to_f64(o), lse.cpu().double().numpy(), o_ref, lse_ref, w.name)
