@@ -84,12 +84,19 @@ __device__ __forceinline__ void wait_vmcnt() {
 // otherwise assume that any later LDS read may alias the in-flight load and wait for every
 // outstanding load first. Completion is ordered explicitly instead (vmcnt wait on the issuing wave,
 // then a workgroup barrier) before any wave reads the destination. The SALU write of M0 needs one
-// wait state before the load.
+// wait state before the load. NT: non-temporal (data that is read once and not kept in the caches).
+template <bool NT = false>
 __device__ __forceinline__ void dma16_buffer(u32x4 rsrc, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
-               :
-               : "v"(voff), "s"(rsrc), "s"(lds)
-               : "memory", "m0");
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen nt lds"
+                 :
+                 : "v"(voff), "s"(rsrc), "s"(lds)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+                 :
+                 : "v"(voff), "s"(rsrc), "s"(lds)
+                 : "memory", "m0");
 }
 __device__ __forceinline__ uint32_t lds_offset(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
@@ -105,7 +112,8 @@ __device__ __forceinline__ void compiler_fence() { asm volatile("" : : : "memory
 // access (their scores are masked and their V rows meet P = 0), which also makes the loads of tiles
 // past the last one cheap. One head's K or V spans less than 4 GiB (the API bounds Sk * d), so
 // 32-bit record counts suffice.
-template <int NWAVES, int BN, int CH>
+// NT: non-temporal loads.
+template <int NWAVES, int BN, int CH, bool NT = false>
 struct TileLoader {
   static constexpr int NI = BN * CH / 64 / NWAVES;  // loads per wave per tile
   static constexpr uint32_t kRowBytes = CH * 16;
@@ -152,7 +160,7 @@ struct TileLoader {
     return lds_offset(slot + wave * NI * 1024);
   }
   __device__ __forceinline__ void issue_one(const u32x4& r, uint32_t l, int i) const {
-    dma16_buffer(r, voff[i], l + i * 1024);
+    dma16_buffer<NT>(r, voff[i], l + i * 1024);
   }
   // Issue all loads of the tile at key n0 into `slot` at once.
   __device__ __forceinline__ void issue(int n0, unsigned char* slot, int wave) const {

@@ -12,19 +12,20 @@
 // 2 * (d_qk + d_v) flops: the whole path's intensity is below d / 2 flop per byte (Sec. "The
 // Operational Intensity Constraint", Table 3), under MI355X's ridge point for any head dimension
 // here, so every kernel is written to stream HBM:
-//  * scores: one workgroup per block of 128 query rows. The block's Q rows stay in registers as the
+//  * scores: one workgroup per block of 128 query rows, four waves that compute and one that loads K. The block's Q rows stay in registers as the
 //    B operand of S^T = K Q^T (v_mfma_f32_32x32x16_bf16); 64-key K tiles go HBM/L2 -> LDS through
 //    the direct-to-LDS buffer loads of the fused kernel, two tiles ahead in a three-slot ring (one
 //    tile ahead in two slots for d_qk = 192). With
 //    the K rows in the permuted order perm32, each lane's accumulator holds 8 consecutive keys of
 //    one query row per register group; the tile is staged through LDS so that every store writes
 //    whole 128-byte row segments.
-//  * softmax: one wavefront per row, 16-byte loads and stores (1 KiB contiguous per instruction).
-//    A row of up to 8192 keys stays in registers between the statistics and the write; longer rows
-//    are read twice.
+//  * softmax: one wavefront per row, 16-byte loads and stores (1 KiB contiguous per instruction), in
+//    instances for rows of up to 512, 1024, .., 8192 keys that stay in registers between the statistics
+//    and the write; longer rows are read twice.
 //  * P V: one workgroup per block of 128 query rows computing O^T = V^T P^T; P and V tiles both go
 //    HBM -> LDS by direct-to-LDS loads (P in whole 128-byte row segments) through a ring, and V is
 //    read with ds_read_b64_tr_b16 as in the fused kernel.
+//  * A spill too large for the caches is stored and loaded non-temporally (STREAM).
 //  * Causal masking: no kernel touches keys past a block's extent (the visible keys of its last row,
 //    rounded up to 64); the softmax writes the masked entries inside the extent as zeros, so the
 //    P V product needs no mask. Block order and XCD placement follow the fused kernel (heaviest
@@ -85,6 +86,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(void* base, uint32_t
   return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)bytes, 0x00020000);
 }
 
+constexpr int kNonTemporal = 2;  // cache policy operand of buffer loads and stores
+
 template <int N>
 __device__ __forceinline__ void fenced_wait() {
   compiler_fence();
@@ -99,8 +102,19 @@ __device__ __forceinline__ void block_barrier() {
 
 // ---- 1. scores ------------------------------------------------------------------------------------
 
-template <int DQK>
-__global__ __launch_bounds__(kWaves * 64) void lbl_scores_kernel(LblParams p) {
+// Bound by the store of S (2 bytes per 2 d_qk flops).
+//  * A fifth wave issues every K load and waits for them, so that the waves that compute wait for no
+//    load: the vmcnt counter retires in issue order, so a wait for a K tile issued behind earlier stores
+//    of S also waited for those stores' acknowledgement (32 heads S1024 d128 causal 17.4 -> 16.5 us).
+//  * STREAM (see streams()): S is stored non-temporally, so that it
+//    does not push its own earlier lines through the cache, and the workgroups start their key sweeps at
+//    different tiles: in step, all of them write the same key columns of rows a power of two apart.
+//    32 heads S4096 d128: causal 175 -> 134 us (537 MB, 4.0 TB/s), full 320 -> 246 us (4.4 TB/s); the
+//    non-temporal stores alone 148 and 270, the sweeps alone 195 and 297, neither 212 and 454.
+constexpr int kScoreThreads = (kWaves + 1) * 64;
+
+template <int DQK, bool STREAM>
+__global__ __launch_bounds__(kScoreThreads) void lbl_scores_kernel(LblParams p) {
   constexpr int KS = DQK / 16;                          // k-steps of the product
   constexpr int KCH = DQK / 8;                          // 16-byte chunks per K row
   constexpr int K_BYTES = kLblKeys * DQK * 2;
@@ -108,10 +122,9 @@ __global__ __launch_bounds__(kWaves * 64) void lbl_scores_kernel(LblParams p) {
   // workgroup's LDS at 64 KiB (two workgroups per CU).
   constexpr int NKR = DQK >= 192 ? 2 : 3;
   constexpr int D = NKR - 1;
-  constexpr int KL = kLblKeys * KCH / 64 / kWaves;      // direct-to-LDS loads per wave per tile
+  constexpr int KL = kLblKeys * KCH / 64;               // direct-to-LDS loads per tile
   constexpr int NST = 4;                                // S stores per wave per tile
-  static_assert(KL * 64 * kWaves == kLblKeys * KCH, "tile split over waves");
-  static_assert(KL + 2 * NST < 64, "vmcnt range");
+  static_assert(D * KL < 64, "vmcnt range");
   constexpr int STAGE = 32 * kLblKeys * 2;              // one wave's 32 x 64 tile of S, bf16
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NKR * K_BYTES + kWaves * STAGE];
 
@@ -123,6 +136,27 @@ __global__ __launch_bounds__(kWaves * 64) void lbl_scores_kernel(LblParams p) {
   const int64_t kvh = (int64_t)(bh / p.hq) * p.hkv + (bh % p.hq) / p.group;
   const int nt = lbl_extent(p, qb) / kLblKeys;
   const int rows_here = min(kLblRows, p.sq - qb * kLblRows);
+  auto kslot = [&](int t) { return smem + (t % NKR) * K_BYTES; };
+  // Key tile of step j: the sweep starts at tile `first` and wraps (steps from nt on load nothing).
+  const int first = STREAM && nt > 0 ? (int)((unsigned)(bh * 37 + qb * 11) % (unsigned)nt) : 0;
+  auto tile = [&](int j) { return !STREAM || j >= nt ? j : j + first >= nt ? j + first - nt : j + first; };
+  if (wave == kWaves) {
+    // The loads go K0 .. K(D-1), then per step j: K(j+D). Before step j, K(j) must have landed; issued
+    // after it are the D - 1 tiles after it.
+    TileLoader<1, kLblKeys, KCH> kload;
+    kload.init(p.k + kvh * p.sk * DQK, min(p.sk, nt * kLblKeys), 0, lane, [](int r) { return k_swizzle<DQK>(r); });
+#pragma unroll
+    for (int t = 0; t < D; ++t) kload.issue(tile(t) * kLblKeys, kslot(t), 0);
+    for (int j = 0; j < nt; ++j) {
+      fenced_wait<(D - 1) * KL>();
+      // The barrier publishes K(j) and ensures every wave is done with step j-1, whose slot K(j+D) reuses.
+      block_barrier();
+      kload.issue(tile(j + D) * kLblKeys, kslot(j + D), 0);
+    }
+    // No direct-to-LDS load may still be in flight when the workgroup exits.
+    fenced_wait<0>();
+    return;
+  }
   const int rl = wave * 32 + i32;  // this lane's query row in the block
 
   // Q rows as B operands: lane (i32, h) holds row rl, dims 16*ks + 8*h .. +7. Padding rows of the last
@@ -131,10 +165,6 @@ __global__ __launch_bounds__(kWaves * 64) void lbl_scores_kernel(LblParams p) {
   const uint16_t* qrow = p.q + ((int64_t)bh * p.sq + qb * kLblRows + min(rl, rows_here - 1)) * DQK + 8 * h;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qrow + 16 * ks);
-
-  TileLoader<kWaves, kLblKeys, KCH> kload;
-  kload.init(p.k + kvh * p.sk * DQK, min(p.sk, nt * kLblKeys), wave, lane, [](int r) { return k_swizzle<DQK>(r); });
-  auto kslot = [&](int t) { return smem + (t % NKR) * K_BYTES; };
 
   const __amdgpu_buffer_rsrc_t out = make_rsrc(p.s + lbl_chunk_row(p, bh, qb) * p.ld, (uint32_t)(rows_here * p.ld * 2));
   // The wave's tile goes through LDS so that each store writes 8 whole 128-byte row segments (lane l:
@@ -146,23 +176,8 @@ __global__ __launch_bounds__(kWaves * 64) void lbl_scores_kernel(LblParams p) {
   const int st_row = lane >> 3, st_c = lane & 7;
   const uint32_t out_off = (uint32_t)((wave * 32 + st_row) * p.ld + 8 * st_c) * 2u;
 
-  // Per wave the vector-memory instructions go: K0 .. K(D-1), then per step j: K(j+D), S(j) (4
-  // stores). Before step j, K(j) must have landed; issued after it are: for j >= D, S(j-D) and the
-  // D - 1 steps after it (a K tile and 4 stores each); for j < D, K(j+1) .. K(D-1) and the j steps so
-  // far. Vector memory operations complete in issue order for the counter.
-  static_assert(D == 1 || D == 2, "prefetch distance");
-#pragma unroll
-  for (int t = 0; t < D; ++t) kload.issue(t * kLblKeys, kslot(t), wave);
   for (int j = 0; j < nt; ++j) {
-    if (j >= D)
-      fenced_wait<NST + (D - 1) * (KL + NST)>();
-    else if (j == 1)
-      fenced_wait<KL + NST>();  // D == 2
-    else
-      fenced_wait<(D - 1) * KL>();
-    // The barrier publishes K(j) and ensures every wave is done with step j-1, whose slot K(j+D) reuses.
-    block_barrier();
-    kload.issue((j + D) * kLblKeys, kslot(j + D), wave);
+    block_barrier();  // K(j) has landed
     const unsigned char* sK = kslot(j);
     f32x16 acc[2];
 #pragma unroll
@@ -188,29 +203,41 @@ __global__ __launch_bounds__(kWaves * 64) void lbl_scores_kernel(LblParams p) {
         const int c = 4 * kb + 2 * g + h;
         *reinterpret_cast<u32x4*>(stage + i32 * 128 + ((c ^ ((i32 >> 1) & 7)) << 4)) = w;
       }
-    const uint32_t tile_off = out_off + (uint32_t)(j * kLblKeys) * 2u;
+    const uint32_t tile_off = out_off + (uint32_t)(tile(j) * kLblKeys) * 2u;
 #pragma unroll
     for (int st = 0; st < NST; ++st) {
       const int r = 8 * st + st_row;
       const u32x4 w = *reinterpret_cast<const u32x4*>(stage + r * 128 + ((st_c ^ ((r >> 1) & 7)) << 4));
-      __builtin_amdgcn_raw_buffer_store_b128(w, out, (int)(tile_off + (uint32_t)(8 * st * p.ld) * 2u), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(w, out, (int)(tile_off + (uint32_t)(8 * st * p.ld) * 2u), 0, STREAM ? kNonTemporal : 0);
     }
   }
-  // No direct-to-LDS load may still be in flight when the workgroup exits.
-  fenced_wait<0>();
 }
 
 // ---- 2. mask + softmax ------------------------------------------------------------------------------
 
+// Reductions over the 64 lanes, the result on every lane: rotations by 8, 4, 2 and 1 inside each row of 16
+// lanes (DPP), then the exchanges between the rows of 16 and the halves of 32 lanes. All of it is VALU
+// work; the same butterfly through __shfl_xor costs an LDS round trip per stage.
+template <int CTRL>
+__device__ __forceinline__ float dpp_row(float x) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+constexpr int kRowRor = 0x120;  // DPP control of a rotation within a row of 16 lanes, plus the distance
 __device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-  return x;
+  x = fmaxf(x, dpp_row<kRowRor + 8>(x));
+  x = fmaxf(x, dpp_row<kRowRor + 4>(x));
+  x = fmaxf(x, dpp_row<kRowRor + 2>(x));
+  x = fmaxf(x, dpp_row<kRowRor + 1>(x));
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return half_swap_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
 }
 __device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-  return x;
+  x += dpp_row<kRowRor + 8>(x);
+  x += dpp_row<kRowRor + 4>(x);
+  x += dpp_row<kRowRor + 2>(x);
+  x += dpp_row<kRowRor + 1>(x);
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return half_swap_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
 // Element e (0..7) of a 16-byte chunk of bf16, widened to fp32 (exact).
@@ -223,17 +250,31 @@ __device__ __forceinline__ float chunk_elem(const u32x4& c, int e) {
 // 64 * NCH: lane l holds chunks g0 + 64 t + l. Masked keys are replaced by bf16 -inf as they are
 // loaded, so the arithmetic below needs no mask: their exponentials are 0 and they never win a
 // maximum. Chunks past the row are skipped with wave-uniform branches.
-template <int NCH>
+//
+// Bound by HBM (read S, write P) while the spill exceeds the Infinity Cache, and there within 3 % of a
+// device copy (32 heads S4096 causal 1 074 MB in 212 us, 5.1 TB/s); below that by the chain load -
+// maximum - sum - store of a row and the waves in flight to hide it. NCH is therefore the least that
+// holds a row (16 steps of registers and branches for a 512-key row took twice the time), and the
+// reductions stay in the VALU: B8 H12 S512 40.6 -> 19.3 us, 32 heads S1024 causal 32.5 -> 16.5, 64 heads
+// S2048 causal 166 -> 99. Two, four or eight rows per wave were slower at every length measured.
+// STREAM (see streams()): S is read and P written non-temporally.
+template <int NCH, bool STREAM>
 __global__ __launch_bounds__(256) void lbl_softmax_kernel(LblParams p) {
   constexpr float kLog2e = 1.44269504088896340736f;
   constexpr float kLn2 = 0.69314718055994530942f;
   constexpr uint32_t kNegInf2 = 0xff80ff80u;  // two bf16 -inf
   constexpr int GROUP = 64 * NCH;             // chunks per register-resident group of a row
   const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t r = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (r >= p.rows) return;
-  const int bh = p.bh0 + (int)(r / p.sq);
-  const int i = p.qb0 * kLblRows + (int)(r % p.sq);
+  // Row r of the chunk is row i of head bh; a 64-bit division only where 32 bits do not hold r.
+  int64_t hd = 0;
+  if (p.rows <= UINT32_MAX)
+    hd = (uint32_t)r / (uint32_t)p.sq;
+  else
+    hd = r / p.sq;
+  const int bh = p.bh0 + (int)hd;
+  const int i = p.qb0 * kLblRows + (int)(r - hd * p.sq);
   const int nvis = p.causal ? max(0, min(p.sk, i + 1 + p.sk - p.sq)) : p.sk;
   const int nr = (nvis + 7) / 8;                    // chunks holding a visible key
   const int nw = lbl_extent(p, i / kLblRows) / 8;   // chunks written
@@ -248,17 +289,26 @@ __global__ __launch_bounds__(256) void lbl_softmax_kernel(LblParams p) {
     for (int t = 0; t < NCH; ++t) {
       if (t < nt) {
         const int c = g0 + t * 64 + lane;
-        u32x4 x = c < nr ? src[c] : u32x4{kNegInf2, kNegInf2, kNegInf2, kNegInf2};
-        if (c == nr - 1 && (nvis & 7)) {  // the chunk with the last visible key: mask its tail
+        u32x4 x = {kNegInf2, kNegInf2, kNegInf2, kNegInf2};
+        if (c < nr) x = STREAM ? __builtin_nontemporal_load(src + c) : src[c];
+        buf[t] = x;
+      }
+    }
+    // Mask the tail of the chunk with the last visible key, after all loads are issued.
+    const int tail = nvis & 7;
+    if (tail != 0) {
+#pragma unroll
+      for (int t = 0; t < NCH; ++t) {
+        const int last = nr - 1 - (g0 + t * 64);  // lane of that chunk, if it is in this step
+        if (last >= 0 && last < 64 && lane == last) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const int k0 = 2 * e - (nvis & 7);  // element 2e is visible iff k0 < 0
-            const uint32_t lo = k0 < 0 ? (x[e] & 0xffffu) : 0xff80u;
-            const uint32_t hi = k0 + 1 < 0 ? (x[e] & 0xffff0000u) : 0xff800000u;
-            x[e] = lo | hi;
+            const int k0 = 2 * e - tail;  // element 2e is visible iff k0 < 0
+            const uint32_t lo = k0 < 0 ? (buf[t][e] & 0xffffu) : 0xff80u;
+            const uint32_t hi = k0 + 1 < 0 ? (buf[t][e] & 0xffff0000u) : 0xff800000u;
+            buf[t][e] = lo | hi;
           }
         }
-        buf[t] = x;
       }
     }
   };
@@ -314,7 +364,12 @@ __global__ __launch_bounds__(256) void lbl_softmax_kernel(LblParams p) {
             w[e] = pack_bf16x2(__builtin_amdgcn_exp2f(fmaf(chunk_elem(buf[t], 2 * e), kLog2e, -off)),
                                __builtin_amdgcn_exp2f(fmaf(chunk_elem(buf[t], 2 * e + 1), kLog2e, -off)));
         }
-        if (c < nw) dst[c] = w;
+        if (c < nw) {
+          if constexpr (STREAM)
+            __builtin_nontemporal_store(w, dst + c);
+          else
+            dst[c] = w;
+        }
       }
     }
   }
@@ -326,7 +381,10 @@ __global__ __launch_bounds__(256) void lbl_softmax_kernel(LblParams p) {
 #define FA_LBL_PV_SLOTS 2
 #endif
 
-template <int DV>
+// STREAM (see streams()): P is loaded non-temporally (32 heads S4096 d128: causal 129 -> 113 us, 537 MB at
+// 4.8 TB/s, full 211 -> 201 us). A third P slot (two tiles ahead) was 2-11 % slower, staggered key sweeps as
+// in the scores kernel 1-4 % slower below the Infinity Cache and level above.
+template <int DV, bool STREAM>
 __global__ __launch_bounds__(kWaves * 64) void lbl_pv_kernel(LblParams p) {
   constexpr int DB = DV / 32;                           // 32-dim blocks of the output
   constexpr int VCH = DV / 8;                           // 16-byte chunks per V row
@@ -390,7 +448,7 @@ __global__ __launch_bounds__(kWaves * 64) void lbl_pv_kernel(LblParams p) {
                       0x00020000u};
     const uint32_t l = lds_offset(pslot(t) + wave * PL * 1024);
 #pragma unroll
-    for (int i = 0; i < PL; ++i) dma16_buffer(rs, p_voff[i], l + i * 1024);
+    for (int i = 0; i < PL; ++i) dma16_buffer<STREAM>(rs, p_voff[i], l + i * 1024);
   };
   // B operand P^T[keys 16*ps + 0..15][rows of the wave]: lane (i32, h) reads row rl, chunk 2*ps + h.
   auto pfrag = [&](const unsigned char* sP, int ps) {
@@ -442,30 +500,69 @@ __global__ __launch_bounds__(kWaves * 64) void lbl_pv_kernel(LblParams p) {
 bool lbl_scores_supported(int d_qk) { return d_qk == 64 || d_qk == 128 || d_qk == 192; }
 bool lbl_pv_supported(int d_v) { return d_v == 64 || d_v == 128; }
 
-hipError_t launch_lbl_scores(const LblParams& p, int d_qk, hipStream_t stream) {
-  const dim3 grid(p.nbh * p.nqb), block(kWaves * 64);
+// Whether the chunk's spill (2 bytes per visible score) is streamed past the caches: when it and the rest of
+// the traffic no longer fit the 256 MB Infinity Cache, so that the next operator finds little of it there
+// in any case. Measured on the whole path, streamed against cached (interleaved, one box): 512 MiB (32 heads
+// S4096 causal) 444 against 561 us, 192 MiB (24 heads S2048) 178 against 200, 143 MiB (6 heads S5000 causal)
+// 200 against 190, 128 MiB (16 heads S2048) 113 against 100, (32 heads S2048 causal) 148 against 159,
+// 32 MiB (32 heads S1024 causal) 53 against 50, 48 MiB (B8 H12 S512) 49 against 45.
+static bool streams(const LblParams& p) {
+  constexpr double kStreamBytes = 160.0 * (1 << 20);
+  const double sq = p.sq, sk = p.sk;
+  const double keys = !p.causal ? sk : sk >= sq ? sk - sq + (sq + 1) / 2 : sk * (sk + 1) / 2 / sq;  // mean per row
+  return 2.0 * (double)p.rows * keys > kStreamBytes;
+}
+
+template <bool STREAM>
+static hipError_t launch_scores(const LblParams& p, int d_qk, hipStream_t stream) {
+  const dim3 grid(p.nbh * p.nqb), block(kScoreThreads);
   switch (d_qk) {
-    case 64: hipLaunchKernelGGL(lbl_scores_kernel<64>, grid, block, 0, stream, p); break;
-    case 128: hipLaunchKernelGGL(lbl_scores_kernel<128>, grid, block, 0, stream, p); break;
-    case 192: hipLaunchKernelGGL(lbl_scores_kernel<192>, grid, block, 0, stream, p); break;
+    case 64: hipLaunchKernelGGL((lbl_scores_kernel<64, STREAM>), grid, block, 0, stream, p); break;
+    case 128: hipLaunchKernelGGL((lbl_scores_kernel<128, STREAM>), grid, block, 0, stream, p); break;
+    case 192: hipLaunchKernelGGL((lbl_scores_kernel<192, STREAM>), grid, block, 0, stream, p); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <bool STREAM>
+static hipError_t launch_softmax(const LblParams& p, hipStream_t stream) {
+  const dim3 grid((unsigned)((p.rows + 3) / 4)), block(256);
+  const int steps = (p.ld / 8 + 63) / 64;  // 64-chunk steps of a whole row
+  if (steps <= 1)
+    hipLaunchKernelGGL((lbl_softmax_kernel<1, STREAM>), grid, block, 0, stream, p);
+  else if (steps <= 2)
+    hipLaunchKernelGGL((lbl_softmax_kernel<2, STREAM>), grid, block, 0, stream, p);
+  else if (steps <= 4)
+    hipLaunchKernelGGL((lbl_softmax_kernel<4, STREAM>), grid, block, 0, stream, p);
+  else if (steps <= 8)
+    hipLaunchKernelGGL((lbl_softmax_kernel<8, STREAM>), grid, block, 0, stream, p);
+  else
+    hipLaunchKernelGGL((lbl_softmax_kernel<16, STREAM>), grid, block, 0, stream, p);
+  return hipGetLastError();
+}
+
+template <bool STREAM>
+static hipError_t launch_pv(const LblParams& p, int d_v, hipStream_t stream) {
+  const dim3 grid(p.nbh * p.nqb), block(kWaves * 64);
+  switch (d_v) {
+    case 64: hipLaunchKernelGGL((lbl_pv_kernel<64, STREAM>), grid, block, 0, stream, p); break;
+    case 128: hipLaunchKernelGGL((lbl_pv_kernel<128, STREAM>), grid, block, 0, stream, p); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_lbl_scores(const LblParams& p, int d_qk, hipStream_t stream) {
+  return streams(p) ? launch_scores<true>(p, d_qk, stream) : launch_scores<false>(p, d_qk, stream);
 }
 
 hipError_t launch_lbl_softmax(const LblParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL(lbl_softmax_kernel<16>, dim3((unsigned)((p.rows + 3) / 4)), dim3(256), 0, stream, p);
-  return hipGetLastError();
+  return streams(p) ? launch_softmax<true>(p, stream) : launch_softmax<false>(p, stream);
 }
 
 hipError_t launch_lbl_pv(const LblParams& p, int d_v, hipStream_t stream) {
-  const dim3 grid(p.nbh * p.nqb), block(kWaves * 64);
-  switch (d_v) {
-    case 64: hipLaunchKernelGGL(lbl_pv_kernel<64>, grid, block, 0, stream, p); break;
-    case 128: hipLaunchKernelGGL(lbl_pv_kernel<128>, grid, block, 0, stream, p); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return streams(p) ? launch_pv<true>(p, d_v, stream) : launch_pv<false>(p, d_v, stream);
 }
 
 }  // namespace fa
