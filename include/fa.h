@@ -148,7 +148,8 @@ size_t fa_fwd_split_workspace_bytes(int B, int Hq, int Sq, int d_v, int n_split)
  *                call's work on `stream` has completed. NULL only when no byte is needed.
  *   workspace_bytes  its size in bytes
  *
- * Enqueues two kernels on `stream`. Errors: n_parts < 1 (FA_ERR_BAD_SHAPE); then sizes
+ * Enqueues two kernels on `stream` (with n_parts == 1 only the first, which writes O and LSE itself
+ * and leaves the workspace untouched). Errors: n_parts < 1 (FA_ERR_BAD_SHAPE); then sizes
  * (FA_ERR_BAD_SHAPE), head dimensions (FA_ERR_UNSUPPORTED), pointers
  * (FA_ERR_NULL_POINTER), scale (FA_ERR_BAD_SCALE), alignment (FA_ERR_UNSUPPORTED), index ranges
  * (FA_ERR_BAD_SHAPE); B*Hq*Sq == 0 returns FA_OK without touching the workspace; then more than

@@ -18,7 +18,7 @@
 //    O^T += V^T P^T (V read with ds_read_b64_tr_b16).
 //  * The waves' (m, l, O) are combined through LDS (log-sum-exp weights) and the workgroup writes
 //    its part's O, normalised by the part's own sum, and the part's LSE; the merge kernel of split mode
-//    combines the parts.
+//    combines the parts. A single part is written as the result at once.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -62,7 +62,7 @@ struct DecCfg {
   static_assert(K_LOADS * 64 == 32 * KCH && V_LOADS * 64 == 32 * VCH, "wave-private tile rows");
 };
 
-template <int DQK, int DV>
+template <int DQK, int DV, bool STREAM>
 __global__ __attribute__((amdgpu_flat_work_group_size(kDecWaves * 64, kDecWaves * 64)))
 void fa_decode_kernel(DecodeParams p) {
   using C = DecCfg<DQK, DV>;
@@ -99,8 +99,8 @@ void fa_decode_kernel(DecodeParams p) {
 
   const uint16_t* kh = p.k + (int64_t)bg * p.sk * DQK;
   const uint16_t* vh = p.v + (int64_t)bg * p.sk * DV;
-  TileLoader<kDecWaves, kDecKeys, C::KCH> kload;
-  TileLoader<kDecWaves, kDecKeys, C::VCH> vload;
+  TileLoader<kDecWaves, kDecKeys, C::KCH, STREAM> kload;
+  TileLoader<kDecWaves, kDecKeys, C::VCH, STREAM> vload;
   kload.init(kh, k_end, wave, lane, [](int r) { return k_swizzle<DQK>(r); });
   vload.init(vh, k_end, wave, lane, [](int r) { return v_swizzle<DV>(r); });
   auto kslot = [&](int t) { return smem + (t % kDecSlots) * C::SLOT; };
@@ -232,17 +232,33 @@ void fa_decode_kernel(DecodeParams p) {
     const float inv = L > 0.f ? 1.f / L : 0.f;
     const int cm = (c0 + col) / p.sq, ci = (c0 + col) % p.sq;
     const int64_t orow_g = ((int64_t)b * p.hq + g * p.group + cm) * p.sq + ci;
-    float* dst = p.o_part + ((int64_t)part * p.total_rows + orow_g) * DV + d0;
+    f32x4 o[DV / TPC / 4];
 #pragma unroll
     for (int d = 0; d < DV / TPC; d += 4) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int w = 0; w < kDecWaves; ++w)
         acc += wt[w] * *reinterpret_cast<const f32x4*>(ob + (w * 32 + col) * C::OROW + d0 + d);
-      *reinterpret_cast<f32x4*>(dst + d) = acc * inv;
+      o[d / 4] = acc * inv;
     }
-    if (tid % TPC == 0)
-      p.lse_part[(int64_t)part * p.total_rows + orow_g] = L > 0.f ? (M + log2f(L)) * 0.69314718055994530942f : -INFINITY;
+    const float lse = L > 0.f ? (M + log2f(L)) * 0.69314718055994530942f : -INFINITY;
+    if (p.n_parts == 1) {
+      // The only part is the result (what the merge would make of it, bit for bit): no partial results
+      // and no merge kernel (B64 64/8, 600 keys d128 34.7 -> 30.9 us, B32 32/8, 2048 keys d64 25.1 -> 22.1).
+      uint16_t* dst = p.o + orow_g * DV + d0;
+#pragma unroll
+      for (int d = 0; d < DV / TPC; d += 8) {
+        const f32x4 x = o[d / 4], y = o[d / 4 + 1];
+        *reinterpret_cast<u32x4*>(dst + d) =
+            u32x4{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+      }
+      if (tid % TPC == 0 && p.lse != nullptr) p.lse[orow_g] = lse;
+    } else {
+      float* dst = p.o_part + ((int64_t)part * p.total_rows + orow_g) * DV + d0;
+#pragma unroll
+      for (int d = 0; d < DV / TPC; d += 4) *reinterpret_cast<f32x4*>(dst + d) = o[d / 4];
+      if (tid % TPC == 0) p.lse_part[(int64_t)part * p.total_rows + orow_g] = lse;
+    }
   }
 }
 
@@ -250,7 +266,16 @@ template <int DQK, int DV>
 hipError_t launch_decode_instance(const DecodeParams& p, hipStream_t stream) {
   DecodeParams a = p;
   void* args[] = {&a};
-  return hipLaunchKernel(reinterpret_cast<const void*>(&fa_decode_kernel<DQK, DV>),
+  // K and V are loaded non-temporally when they are read once (one column block) and are more than half
+  // the 256 MB Infinity Cache, so that an earlier pass leaves nothing to find there: allocating lines that
+  // nobody reads again costs bandwidth. Measured against plain loads (interleaved, one box): 512 MiB (128K
+  // keys, 32/8 heads) 97.8 -> 84.7 us, 256 MiB (B16, 4099 keys) 51.2 -> 45.5 and (B64, 1025 keys) 52.4 ->
+  // 45.6, 150 MiB (B64 64/8, 600 keys) 30.9 -> 29.3; at 128 MiB 27.5 -> 26.4 (d = 128) and 22.1 -> 23.0
+  // (d = 64), at 64 MiB level, below (59 MiB, d = 64) 16.1 -> 17.0.
+  constexpr double kStreamBytes = 128.0 * (1 << 20);
+  const bool stream_kv = p.n_cb == 1 && 2.0 * p.batch * p.hkv * p.sk * (DQK + DV) > kStreamBytes;
+  return hipLaunchKernel(stream_kv ? reinterpret_cast<const void*>(&fa_decode_kernel<DQK, DV, true>)
+                                   : reinterpret_cast<const void*>(&fa_decode_kernel<DQK, DV, false>),
                          dim3((unsigned)(p.batch * p.hkv * p.n_cb * p.n_parts)), dim3(kDecWaves * 64), args, 0,
                          stream);
 }
@@ -273,7 +298,7 @@ hipError_t launch_decode(DecodeParams p, int d_qk, int d_v, hipStream_t stream) 
     e = launch_decode_instance<192, 128>(p, stream);
   else
     return hipErrorInvalidValue;
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || p.n_parts == 1) return e;  // one part writes O and LSE itself
   MergeParams m;
   m.o_part = p.o_part;
   m.lse_part = p.lse_part;

@@ -1,5 +1,6 @@
-"""GPU tests of the instances chosen by the size of the data: the layer-by-layer operators load and store
-non-temporally when their data is large, and the softmax kernel has an instance per row length."""
+"""GPU tests of the instances chosen by the size of the data: the layer-by-layer operators and the decode
+kernel load and store non-temporally when their data is large, the softmax kernel has an instance per row
+length, and a decode call of a single part writes its result without the merge."""
 
 import pytest
 import torch
@@ -7,6 +8,8 @@ import torch
 import paper_2609_21264_amd as fa
 import test_gpu_lbl as lbl
 import workloads as W
+from oracle import naive_attention
+from parity import compare, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -43,3 +46,49 @@ def test_softmax_row_lengths(sk, causal):
     end inside the last 64-chunk steps. Checks and tolerances of the operator's own test."""
     w = W.small(f"row length {sk}", Hq=1, Hkv=1, Sq=5, Sk=sk, causal=causal, seed=900 + sk)
     lbl.test_softmax_operator(w, True)
+
+
+def _decode(q, k, v, causal, parts):
+    B, Hq, Sq, dqk = q.shape
+    _, Hkv, Sk, dv = v.shape
+    o = torch.full((B, Hq, Sq, dv), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.full((B, Hq, Sq), float("nan"), dtype=torch.float32, device="cuda")
+    fa.forward(q, k, v, causal=causal, return_lse=True, out=o, lse=lse, n_split=parts, decode=True)
+    return o, lse
+
+
+@pytest.mark.parametrize("w", [
+    W.small("one part gqa4 d128", dqk=128, dv=128, B=2, Hq=8, Hkv=2, Sq=3, Sk=300, causal=True, seed=91),
+    W.small("one part d64 two column blocks", Hq=20, Hkv=2, Sq=4, Sk=129, causal=False, seed=92),
+    W.small("one part d192", dqk=192, dv=128, Hq=3, Hkv=3, Sq=1, Sk=1000, causal=True, seed=93),
+    W.small("one part rows without keys", dqk=128, dv=128, Hq=2, Hkv=1, Sq=9, Sk=4, causal=True, seed=94),
+], ids=lambda w: w.name)
+def test_single_part_decode(w):
+    """Against the fp64 oracle, and the same bits as two parts of which the second is empty where the keys
+    fit one tile (the merge of one part with an empty one returns that part)."""
+    q, k, v = (x.cuda() for x in W.make_inputs(w))
+    o, lse = _decode(q, k, v, w.causal, 1)
+    o64, lse64 = naive_attention(to_f64(q), to_f64(k), to_f64(v), w.scale, w.causal)
+    compare(to_f64(o), lse.cpu().double().numpy(), o64, lse64, w.name)
+    if w.Sk <= 128:
+        o2, lse2 = _decode(q, k, v, w.causal, 2)
+        assert torch.equal(_bits(o), _bits(o2)) and torch.equal(_bits(lse), _bits(lse2))
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,dqk,dv,parts", [
+    (9, 16, 8, 1, 3999, 128, 128, 2),
+    (17, 8, 8, 2, 4100, 64, 64, 1),
+    (5, 12, 12, 1, 3700, 192, 128, 3),
+])
+def test_streamed_decode_equals_cached(B, Hq, Hkv, Sq, Sk, dqk, dv, parts):
+    """The whole batch (K and V above 128 MiB: streamed) against each request alone (below it), bit for
+    bit: the arithmetic does not depend on the batch."""
+    assert B * Hkv * Sk * (dqk + dv) * 2 > 128 << 20
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    q, k, v = (torch.randn(s, dtype=torch.bfloat16, device="cuda", generator=g)
+               for s in ((B, Hq, Sq, dqk), (B, Hkv, Sk, dqk), (B, Hkv, Sk, dv)))
+    o, lse = _decode(q, k, v, True, parts)
+    for b in range(B):
+        ob, lb = _decode(q[b:b + 1], k[b:b + 1], v[b:b + 1], True, parts)
+        assert torch.equal(_bits(o[b:b + 1]), _bits(ob)) and torch.equal(_bits(lse[b:b + 1]), _bits(lb))
