@@ -1013,7 +1013,8 @@ void fa_fwd_kernel_preload(const uint16_t* a_q, int a_sq, int a_sk, int a_hq, in
 // runs problems with few query blocks (short sequences, few heads), where 256-row blocks leave CUs
 // idle and each block's serial chain of steps sets the time: on the paper's S = 512 and 2048 GPT-2
 // and BERT shapes and the 128K single-head workload it measured 1.2-1.4x faster than the long
-// instance, and slower once the long instance's grid fills the GPU. At d_qk = 192 two waves per SIMD
+// instance, and slower once the long instance's grid fills the GPU. Split mode runs it by a rule of its
+// own (split_short). At d_qk = 192 two waves per SIMD
 // do not fit, so those problems always run the long instance.
 #ifndef FA_BN
 #define FA_BN 64
@@ -1054,9 +1055,9 @@ template <bool CAUSAL>
 struct Instance<64, 64, CAUSAL, false> {
   using C = Cfg<64, 64, 32, 4, 2, CAUSAL, false, 2, 2, 4, 2, 4>;
 };
-template <int DQK, int DV, bool CAUSAL>
+template <int DQK, int DV, bool CAUSAL, bool SPLIT = false>
 struct ShortInstance {
-  using C = Cfg<DQK, DV, 64, 4, 1, CAUSAL, false, 2, DQK >= 128 ? 1 : 2, DQK >= 128 ? 2 : 6, 2, DQK >= 128 ? 3 : 4>;
+  using C = Cfg<DQK, DV, 64, 4, 1, CAUSAL, SPLIT, 2, DQK >= 128 ? 1 : 2, DQK >= 128 ? 2 : 6, 2, DQK >= 128 ? 3 : 4>;
 };
 // The short instance at d = 64 with 128-key tiles, for keys of at least kWideTileKeys: a step then
 // carries 32 MFMAs per wave instead of 16, over which the per-step waits, barrier, load issue and
@@ -1189,6 +1190,24 @@ hipError_t launch_cfg(FwdParams p, hipStream_t stream) {
   }
 }
 
+// Whether a split-mode problem runs the short instance: its blocks of 128 row-heads pad the query rows to
+// fewer than the long instance's 256, or the long instance's grid leaves CUs idle. Split mode has few query
+// rows, so most of a block can be padding. Measured, long against short (interleaved, one box, d = 128
+// causal): 28/4 heads 100 x 20001 (padded to 256 rows against 128) 79.9 -> 57.5 us, 16/16 100 x 32768 83.3
+// -> 67.0, 16/16 300 x 16384 (512 against 384) 86.6 -> 75.3, 32/8 16 x 32768 (64 against 32 rows of four
+// heads) 49.3 -> 40.3, 32/8 64 x 32768 (equal, long grid of 128) 58.0 -> 53.4; d = 64 12/12 90 x 8192 18.6
+// -> 14.5. With equal padding on a full grid the long instance reads each fragment for twice the rows:
+// 32/8 100 x 32768 75.3 against 78.8, 8/1 500 x 131072 253 against 274.
+bool split_short(const FwdParams& p) {
+  constexpr int64_t kCus = 256;
+  const int hw_log = packed_heads_log2(p.group, 4);
+  const int64_t rows_long = 256 >> hw_log, rows_short = 128 >> hw_log;
+  const int64_t blocks_long = (p.sq + rows_long - 1) / rows_long, blocks_short = (p.sq + rows_short - 1) / rows_short;
+  const int64_t heads = (int64_t)p.batch * p.hkv * (p.group >> hw_log);
+  if (heads * blocks_short * p.n_split > INT32_MAX) return false;
+  return blocks_short * rows_short < blocks_long * rows_long || heads * blocks_long * p.n_split < kCus;
+}
+
 template <int DQK, int DV, bool CAUSAL, bool SPLIT>
 hipError_t launch_instance(FwdParams p, Kind kind, hipStream_t stream) {
   if constexpr (!SPLIT && DQK != 192) {
@@ -1204,6 +1223,9 @@ hipError_t launch_instance(FwdParams p, Kind kind, hipStream_t stream) {
       }
       return launch_cfg<typename ShortInstance<DQK, DV, CAUSAL>::C>(p, stream);
     }
+  }
+  if constexpr (SPLIT && DQK != 192) {
+    if (split_short(p)) return launch_cfg<typename ShortInstance<DQK, DV, CAUSAL, true>::C>(p, stream);
   }
   return launch_cfg<typename Instance<DQK, DV, CAUSAL, SPLIT>::C>(p, stream);
 }
