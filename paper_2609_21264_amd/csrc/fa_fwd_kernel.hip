@@ -7,9 +7,10 @@
 // Mapping onto CDNA4:
 //  * A workgroup has NWAVES = 4 wavefronts (one per SIMD) sharing one key/value head; each wave owns
 //    32*QB = 64 query rows of one query head: 256 rows of one head, or 128 rows of 2 heads or 64 rows
-//    of 4 heads of the same GQA group when the group size allows (long instance; the short instance
-//    has 32-row waves and two workgroups per CU, and the key-halves instance two sets of two 32-row
-//    waves that split every key tile between them, with two or three workgroups per CU).
+//    of 4 heads of the same GQA group when the group size allows (long instance, one workgroup per CU,
+//    two at d = 64; the short instance has 32-row waves and two workgroups per CU, the key-halves
+//    instance two sets of two 32-row waves that split every key tile between them, with two or three
+//    workgroups per CU, and the key-quarters instance four waves that share 32 rows).
 //  * Scores are computed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: the K tile (LDS)
 //    is the A operand and the wave's Q rows (AGPRs, loaded once) are the B operand. In the 32x32
 //    accumulator a lane then holds ONE query row (column = lane % 32) and 16 keys, so row
@@ -33,8 +34,8 @@
 //  * 16-byte LDS chunks are XOR-swizzled per row (K: by the reading lane's key slot; V: by the key
 //    mod 4) so that the lanes the LDS serves in one cycle hit 16 different bank slots. The swizzle
 //    is produced by choosing each lane's source offset, since the load writes LDS lane-linearly.
-//  * The output accumulators O and the Q operand live in AGPRs for the whole kernel; scores,
-//    probabilities and LDS fragments use VGPRs.
+//  * The output accumulators O and the Q operand live in AGPRs for the whole kernel where a SIMD holds
+//    one wave (VGPRs otherwise); scores, probabilities and LDS fragments use VGPRs.
 //  * Causal masking skips key tiles above the diagonal entirely and applies the element mask only on
 //    diagonal and tail tiles.
 //  * Workgroup order: heaviest query blocks first when causal, and the workgroups that share a
@@ -234,8 +235,8 @@ struct WorkMap {
 // which of the key/value head's query heads the workgroup takes. Workgroup t runs on XCD t % 8.
 // Logical work items are ordered by chunk of key/value heads (head_chunk heads each, the first
 // head_chunked of the batch's heads in whole chunks; the short and key-parts instances have one chunk),
-// then heaviest query block first (causal), then batch, key/value head and member; each group of `group` consecutive items (the workgroups of one key/value head at one query
-// block) is placed on one XCD, and groups go to XCDs round-robin (`full` = the items in whole spans of
+// then heaviest query block first (causal), then batch, key/value head and member; each group of `group`
+// consecutive items (the workgroups of one key/value head at one query block) is placed on one XCD, and groups go to XCDs round-robin (`full` = the items in whole spans of
 // 8 groups; the rest keep their order). FAST divides through
 // the multiply-high constants, else with the compiler's division sequence (the long instance: there
 // the faster prologue measured no gain in time, and on the 128K workload it shifted the relative
