@@ -290,7 +290,9 @@ int fa_block_rows(int d_qk, int d_v, int causal);
  * results at the end; causal problems of at most 320 blocks at d = 64 and 192 at d = 128, others of at
  * most 64 and 128). The key-parts blocks run as one workgroup each (two halves of 64-key tiles) or, on
  * grids that would leave compute units idle, as two workgroups of 32 rows (four quarters of 128-key
- * tiles). Every instance computes the same function (Eq. (1) by Alg. 1); which one runs
+ * tiles). Reported for at most twice as many keys as query rows; with more keys (a chunk of a prompt
+ * against its cache) problems of 160 to 256 blocks at d = 128 run the long instance, and causal ones of
+ * 201 to 320 at d = 64 the short one. Every instance computes the same function (Eq. (1) by Alg. 1); which one runs
  * follows from the sizes alone. 0 for unsupported head dimensions or negative sizes. Host
  * arithmetic only. */
 int fa_fwd_rows(int B, int Hq, int Sq, int d_qk, int d_v, int causal);

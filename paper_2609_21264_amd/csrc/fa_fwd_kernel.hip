@@ -1137,6 +1137,24 @@ Kind pick_instance(const FwdParams& p, int d_qk, int d_v, bool causal) {
   return blocks <= (d_qk == 64 ? kShortMaxBlocks64 : kShortMaxBlocks128) ? Kind::kShort : Kind::kLong;
 }
 
+// The instance a launch runs: pick_instance, except where the keys are more than twice the query rows (a
+// chunk of a prompt against its cache). Such a grid is flat, all its chains are about equally long with or
+// without the mask, so what a causal triangle gains from small blocks (a shorter longest chain) is not
+// there. Measured (interleaved, one box), pick_instance's choice against this one: d = 128 causal 32/8
+// 1500 x 9000 (192 blocks, halves) 207.9 -> 194.2 us, 20 heads 2000 x 20000 (160) 483 -> 402, 32 heads
+// 1700 x 12000 (224, short) 302 -> 287, without a mask 16 heads 2560 x 8000 (160) 179 -> 161, 32 heads
+// 1900 x 6000 (256) 174 -> 165; at 128 blocks and fewer the halves stay ahead (32/8 1024 x 16384 249
+// against 269 and 316). d = 64 causal, halves against short: 16 heads 4000 x 16000 (256) 268 -> 246, B2
+// H12 2500 x 10000 (240) 170 -> 151; at 168 blocks (28/4 1300 x 5000) 60 against 67.
+constexpr int64_t kFlatLong128 = 160, kFlatHalf64 = 200;
+Kind pick_launch(const FwdParams& p, int d_qk, int d_v, bool causal) {
+  const Kind kind = pick_instance(p, d_qk, d_v, causal);
+  if (kind == Kind::kLong || p.sk <= (int64_t)p.sq * 2) return kind;
+  const int64_t blocks = (int64_t)p.batch * p.hq * ((p.sq + 255) / 256);
+  if (d_qk == 128) return blocks >= kFlatLong128 ? Kind::kLong : kind;
+  return kind == Kind::kHalf && blocks > kFlatHalf64 ? Kind::kShort : kind;
+}
+
 // log2 of the query heads a workgroup of `nwaves` waves packs: 4, 2 or 1 heads, the largest that
 // divides the GQA group size (and the wave count).
 int packed_heads_log2(int group, int nwaves) {
@@ -1233,7 +1251,7 @@ hipError_t launch_instance(FwdParams p, Kind kind, hipStream_t stream) {
 
 template <bool SPLIT>
 hipError_t launch_dims(FwdParams p, int d_qk, int d_v, bool causal, hipStream_t stream) {
-  const Kind sh = SPLIT ? Kind::kLong : pick_instance(p, d_qk, d_v, causal);
+  const Kind sh = SPLIT ? Kind::kLong : pick_launch(p, d_qk, d_v, causal);
   if (d_qk == 64 && d_v == 64)
     return causal ? launch_instance<64, 64, true, SPLIT>(p, sh, stream)
                   : launch_instance<64, 64, false, SPLIT>(p, sh, stream);
