@@ -505,12 +505,18 @@ bool lbl_pv_supported(int d_v) { return d_v == 64 || d_v == 128; }
 // in any case. Measured on the whole path, streamed against cached (interleaved, one box): 512 MiB (32 heads
 // S4096 causal) 444 against 561 us, 192 MiB (24 heads S2048) 178 against 200, 143 MiB (6 heads S5000 causal)
 // 200 against 190, 128 MiB (16 heads S2048) 113 against 100, (32 heads S2048 causal) 148 against 159,
-// 32 MiB (32 heads S1024 causal) 53 against 50, 48 MiB (B8 H12 S512) 49 against 45.
+// 32 MiB (32 heads S1024 causal) 53 against 50, 48 MiB (B8 H12 S512) 49 against 45. A grid of few workgroups
+// is bound by the latency of their loads, so there the line lies higher: 196 MiB in 112 workgroups (2 heads
+// S7168 d64) 234 against 190, 244 MiB in 125 (one head S16000 causal) 476 against 443, but 180 MiB in 240
+// (5 heads S6144 causal) 239 against 261, 357 MiB in 186 (3 heads S7900) 363 against 408 and 512 MiB in 128
+// (one head S16384) 698 against 896.
 static bool streams(const LblParams& p) {
-  constexpr double kStreamBytes = 160.0 * (1 << 20);
+  constexpr double kMiB = 1 << 20;
+  constexpr int kStreamBlocks = 192;
   const double sq = p.sq, sk = p.sk;
   const double keys = !p.causal ? sk : sk >= sq ? sk - sq + (sq + 1) / 2 : sk * (sk + 1) / 2 / sq;  // mean per row
-  return 2.0 * (double)p.rows * keys > kStreamBytes;
+  const double bytes = 2.0 * (double)p.rows * keys;
+  return bytes > 320 * kMiB || (bytes > 160 * kMiB && p.nbh * p.nqb >= kStreamBlocks);
 }
 
 template <bool STREAM>
