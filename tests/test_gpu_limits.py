@@ -111,6 +111,19 @@ def test_fused_short_instance_at_largest_key_length(big):
     check(o, lse, sq, MAX_SK, False, "fused short", group)
 
 
+def test_fused_short_instance_at_largest_key_length_below_160_blocks(big):
+    """75 query heads per key/value head without a mask: 150 query blocks, which the short instance runs
+    also with more than twice as many keys as query rows (from 160 blocks those run the long one)."""
+    sq, _, k, v = big
+    group = 75
+    assert fa.fa_fwd_rows(1, 2 * group, sq, D, D, False) == 128
+    q = torch.zeros(1, 2 * group, sq, D, dtype=torch.bfloat16, device="cuda")
+    q[..., 0] = 1.0
+    o, lse = fa.forward(q, k, v, causal=False, scale=SCALE, return_lse=True)
+    torch.cuda.synchronize()
+    check(o, lse, sq, MAX_SK, False, "fused short", group)
+
+
 def test_split_at_largest_key_length(big):
     sq, q, k, v = big
     o, lse = fa.forward(q, k, v, causal=True, scale=SCALE, return_lse=True, n_split=64)
