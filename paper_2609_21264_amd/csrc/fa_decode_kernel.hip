@@ -243,8 +243,12 @@ void fa_decode_kernel(DecodeParams p) {
     }
     const float lse = L > 0.f ? (M + log2f(L)) * 0.69314718055994530942f : -INFINITY;
     if (p.n_parts == 1) {
-      // The only part is the result (what the merge would make of it, bit for bit): no partial results
-      // and no merge kernel (B64 64/8, 600 keys d128 34.7 -> 30.9 us, B32 32/8, 2048 keys d64 25.1 -> 22.1).
+      // The only part is the result: no partial results and no merge kernel (B64 64/8, 600 keys d128 34.7 ->
+      // 30.9 us, B32 32/8, 2048 keys d64 25.1 -> 22.1). It is what the merge would make of the part: a part
+      // without a sum (no visible key, or a NaN score) has LSE = -inf, which the merge leaves out, so O = 0.
+      if (!(L > 0.f))
+#pragma unroll
+        for (int d = 0; d < DV / TPC / 4; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
       uint16_t* dst = p.o + orow_g * DV + d0;
 #pragma unroll
       for (int d = 0; d < DV / TPC; d += 8) {

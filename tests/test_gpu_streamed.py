@@ -75,6 +75,30 @@ def test_single_part_decode(w):
         assert torch.equal(_bits(o), _bits(o2)) and torch.equal(_bits(lse), _bits(lse2))
 
 
+@pytest.mark.parametrize("d,dv", [(64, 64), (128, 128), (192, 128)])
+def test_single_part_decode_rows_without_a_sum(d, dv):
+    """Rows whose sum is not a number (a NaN in Q, scores that overflow) and rows without a visible key have
+    LSE = -inf and O = 0, whether one part writes the result or the merge does (the second of two parts is
+    empty: the keys fit one tile). A NaN in V stays in its column, and O and LSE of the other rows too are
+    the same bits either way."""
+    w = W.small(f"rows without a sum d{d}", dqk=d, dv=dv, Hq=6, Hkv=2, Sq=2, Sk=1, causal=True, seed=95)
+    for sk in (1, 100):
+        q, k, v = (x.cuda() for x in W.make_inputs(w.with_(Sk=sk)))
+        q[0, 1, 1, 3] = float("nan")
+        q[0, 4, 1], k[0, 1, 0] = 3e38, 1.0  # finite; their product overflows
+        v[0, 0, 0, 5] = float("nan")
+        one, two = _decode(q, k, v, True, 1), _decode(q, k, v, True, 2)
+        for a, b in zip(one, two):
+            assert torch.equal(a.isnan(), b.isnan())
+            assert torch.equal(_bits(a)[~a.isnan()], _bits(b)[~b.isnan()])
+        o, lse = one
+        empty = torch.zeros(6, 2, dtype=torch.bool, device="cuda")
+        empty[1, 1] = empty[4, 1] = True
+        empty[:, 0] = sk == 1  # causal: row 0 of 2 sees no key of 1
+        assert bool((lse[0][empty] == -float("inf")).all()) and bool((o[0][empty] == 0).all())
+        assert bool(lse[0][~empty].isfinite().all())
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,dqk,dv,parts", [
     (9, 16, 8, 1, 3999, 128, 128, 2),
     (17, 8, 8, 2, 4100, 64, 64, 1),
