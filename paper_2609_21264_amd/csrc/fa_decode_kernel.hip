@@ -215,6 +215,7 @@ void fa_decode_kernel(DecodeParams p) {
 
   // Each thread finishes DV / TPC dims of one column: TPC threads per column, 32 columns.
   constexpr int TPC = kDecWaves * 64 / 32;
+  static_assert(DV % (8 * TPC) == 0, "a thread finishes whole 16-byte chunks of the output");
   const int col = tid / TPC, d0 = (tid % TPC) * (DV / TPC);
   if (c0 + col < p.rows) {
     float mw[kDecWaves], M = -INFINITY;

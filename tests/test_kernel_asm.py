@@ -15,6 +15,7 @@
 import os
 import re
 import shutil
+import subprocess
 import tempfile
 
 import pytest
@@ -244,6 +245,21 @@ def test_decode_no_access_to_registers_of_in_flight_loads(decode_asm_text):
     assert kernels
     report = {n: bad[:5] for n, code in kernels.items() if (bad := _in_flight_violations(code))}
     assert not report, report
+
+
+def test_decode_waves_leave_whole_output_chunks():
+    """The decode kernel's wave count is a build parameter. Each thread stores DV / (2 waves) output dims in
+    16-byte chunks, so a count that leaves a part of a chunk (3: ten dims of 64) must not compile; 2 and the
+    default 4 do."""
+    def compiles(waves):
+        cmd = [fa_build.hipcc(), *fa_build._device_flags(), f"-DFA_DEC_WAVES={waves}", "--cuda-device-only", "-w",
+               "-fsyntax-only", os.path.join(fa_build.CSRC, "fa_decode_kernel.hip")]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        return res.returncode == 0, res.stderr
+
+    assert compiles(2)[0] and compiles(4)[0]
+    ok, err = compiles(3)
+    assert not ok and "whole 16-byte chunks" in err, err
 
 
 def test_no_scalar_memory_writes(asm_text, lbl_asm_text, decode_asm_text):
