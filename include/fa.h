@@ -282,20 +282,31 @@ const char* fa_status_str(fa_status_t s);
  * these rows each. Host arithmetic only. */
 int fa_block_rows(int d_qk, int d_v, int causal);
 
-/* Query rows per block holding one query head of the fused-kernel instance that fa_fwd and
- * fa_fwd_ex (without split mode) launch for a problem of B batches, Hq query heads and Sq query rows:
+/* Query rows per block holding one query head of the fused-kernel instance that the grid alone (B
+ * batches, Hq query heads, Sq query rows) selects for fa_fwd and fa_fwd_ex without split mode:
  * 256 (long instance: one workgroup per compute unit, two at d = 64), 128 (short instance: two per
  * compute unit, at most 1024 blocks at d = 64 and 256 at d = 128, i.e. blocks of the long instance's
  * rows) or 64 (key parts: the wave sets of a workgroup take the parts of every key tile and merge their
  * results at the end; causal problems of at most 320 blocks at d = 64 and 192 at d = 128, others of at
- * most 64 and 128). The key-parts blocks run as one workgroup each (two halves of 64-key tiles) or, on
- * grids that would leave compute units idle, as two workgroups of 32 rows (four quarters of 128-key
- * tiles). Reported for at most twice as many keys as query rows; with more keys (a chunk of a prompt
- * against its cache) problems of 160 to 256 blocks at d = 128 run the long instance, and causal ones of
- * 201 to 320 at d = 64 the short one. Every instance computes the same function (Eq. (1) by Alg. 1); which one runs
- * follows from the sizes alone. 0 for unsupported head dimensions or negative sizes. Host
- * arithmetic only. */
+ * most 64 and 128). A call with more than twice as many keys as query rows may run another one, which
+ * this function, having no Sk, cannot tell: fa_fwd_instance does. 0 for unsupported head dimensions or
+ * negative sizes. Host arithmetic only. */
 int fa_fwd_rows(int B, int Hq, int Sq, int d_qk, int d_v, int causal);
+
+/* The fused kernel's instances. Each computes the same function (Eq. (1) by Alg. 1); which one runs
+ * follows from the sizes alone. */
+typedef enum {
+  FA_INSTANCE_NONE = 0,        /* unsupported or invalid sizes, or no query row */
+  FA_INSTANCE_QUARTERS = 1,    /* 32-row workgroups, four waves on the quarters of every 128-key tile */
+  FA_INSTANCE_HALVES = 2,      /* 64 row-heads per workgroup, two wave sets on the halves of every 64-key tile */
+  FA_INSTANCE_SHORT = 3,       /* 128 row-heads per workgroup */
+  FA_INSTANCE_SHORT_WIDE = 4,  /* the same with 128-key tiles (d = 64) */
+  FA_INSTANCE_LONG = 5         /* 256 row-heads per workgroup */
+} fa_instance_t;
+
+/* The instance that fa_fwd and fa_fwd_ex (n_split == 0) or fa_fwd_split (n_split >= 1) launch for these
+ * sizes, decided by the code that launches it. Host arithmetic only. */
+fa_instance_t fa_fwd_instance(int B, int Hq, int Hkv, int Sq, int Sk, int d_qk, int d_v, int causal, int n_split);
 
 #ifdef __cplusplus
 }

@@ -21,6 +21,14 @@ FA_ERR_BAD_SCALE = 4
 FA_ERR_HIP = 5
 FA_ERR_WORKSPACE = 6
 
+# Values of fa_instance_t.
+FA_INSTANCE_NONE = 0
+FA_INSTANCE_QUARTERS = 1
+FA_INSTANCE_HALVES = 2
+FA_INSTANCE_SHORT = 3
+FA_INSTANCE_SHORT_WIDE = 4
+FA_INSTANCE_LONG = 5
+
 #: FA_NOALLOC_SCRATCH_BYTES of include/fa.h: the static scratch behind fa_fwd_decode_noalloc.
 FA_NOALLOC_SCRATCH_BYTES = 32 << 20
 
@@ -28,7 +36,7 @@ FA_NOALLOC_SCRATCH_BYTES = 32 << 20
 EXPORTED = ("fa_fwd", "fa_fwd_ex", "fa_fwd_split", "fa_fwd_split_workspace_bytes", "fa_fwd_split_parts",
             "fa_status_str", "fa_block_rows", "fa_fwd_rows", "fa_lbl_scores", "fa_lbl_softmax", "fa_lbl_pv", "fa_lbl_ld",
             "fa_lbl_workspace_bytes", "fa_fwd_unfused", "fa_fwd_decode", "fa_fwd_decode_parts",
-            "fa_fwd_decode_noalloc")
+            "fa_fwd_decode_noalloc", "fa_fwd_instance")
 
 _lib = None
 
@@ -61,6 +69,8 @@ def load() -> ctypes.CDLL:
     lib.fa_block_rows.restype = i
     lib.fa_fwd_rows.argtypes = [i, i, i, i, i, i]
     lib.fa_fwd_rows.restype = i
+    lib.fa_fwd_instance.argtypes = [i] * 9
+    lib.fa_fwd_instance.restype = i
     lib.fa_lbl_scores.argtypes = [vp, vp, vp, i, i, i, i, i, i, f, i, vp]
     lib.fa_lbl_scores.restype = i
     lib.fa_lbl_softmax.argtypes = [vp, vp, vp, i, i, i, i, i, vp]

@@ -458,4 +458,11 @@ int fa_fwd_rows(int B, int Hq, int Sq, int d_qk, int d_v, int causal) {
   return fa::instance_rows(B, Hq, Sq, d_qk, d_v, causal != 0);
 }
 
+fa_instance_t fa_fwd_instance(int B, int Hq, int Hkv, int Sq, int Sk, int d_qk, int d_v, int causal, int n_split) {
+  static_assert(FA_INSTANCE_QUARTERS == 1 && FA_INSTANCE_HALVES == 2 && FA_INSTANCE_SHORT == 3 &&
+                    FA_INSTANCE_SHORT_WIDE == 4 && FA_INSTANCE_LONG == 5,
+                "launch_instance_id returns these values");
+  return static_cast<fa_instance_t>(fa::launch_instance_id(B, Hq, Hkv, Sq, Sk, d_qk, d_v, causal != 0, n_split));
+}
+
 }  // extern "C"

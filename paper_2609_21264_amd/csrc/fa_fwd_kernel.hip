@@ -1125,8 +1125,9 @@ constexpr int64_t kShortMaxBlocks64 = 1024, kShortMaxBlocks128 = 256;
 // Llama S = 2048 shapes on the slow side), so they stay with it.
 constexpr int64_t kHalfMaxCausal64 = 320, kHalfMaxFull64 = 64, kHalfMaxCausal128 = 192, kHalfMaxFull128 = 128;
 
-enum class Kind { kLong, kShort, kHalf };
+enum class Kind { kLong, kShort, kShortWide, kHalf, kQuarter };
 
+// By the grid alone: kHalf stands for both key-parts instances and kShort for both tile widths.
 Kind pick_instance(const FwdParams& p, int d_qk, int d_v, bool causal) {
   if (!((d_qk == 64 && d_v == 64) || (d_qk == 128 && d_v == 128))) return Kind::kLong;
   const int bm = Instance<64, 64, false>::C::BM;
@@ -1227,31 +1228,33 @@ bool split_short(const FwdParams& p) {
   return blocks_short * rows_short < blocks_long * rows_long || heads * blocks_long * p.n_split < kCus;
 }
 
+// The instance a launch runs (every kind, and split mode's own choice).
+Kind launch_kind(const FwdParams& p, int d_qk, int d_v, bool causal, bool split) {
+  if (split) return d_qk != 192 && split_short(p) ? Kind::kShort : Kind::kLong;
+  const Kind kind = pick_launch(p, d_qk, d_v, causal);
+  if (kind == Kind::kHalf && key_quarters(p, d_qk, causal)) return Kind::kQuarter;
+  if (kind == Kind::kShort && d_qk == 64 && p.sk >= kWideTileKeys) return Kind::kShortWide;
+  return kind;
+}
+
 template <int DQK, int DV, bool CAUSAL, bool SPLIT>
 hipError_t launch_instance(FwdParams p, Kind kind, hipStream_t stream) {
   if constexpr (!SPLIT && DQK != 192) {
-    if (kind == Kind::kHalf) {
-      if (key_quarters(p, DQK, CAUSAL)) return launch_cfg<typename QuarterInstance<DQK, DV, CAUSAL>::C>(p, stream);
-      return launch_cfg<typename HalfInstance<DQK, DV, CAUSAL>::C>(p, stream);
-    }
+    if (kind == Kind::kQuarter) return launch_cfg<typename QuarterInstance<DQK, DV, CAUSAL>::C>(p, stream);
+    if (kind == Kind::kHalf) return launch_cfg<typename HalfInstance<DQK, DV, CAUSAL>::C>(p, stream);
   }
-  if constexpr (!SPLIT && DQK != 192) {
-    if (kind == Kind::kShort) {
-      if constexpr (DQK == 64) {
-        if (p.sk >= kWideTileKeys) return launch_cfg<typename ShortWideInstance<DQK, DV, CAUSAL>::C>(p, stream);
-      }
-      return launch_cfg<typename ShortInstance<DQK, DV, CAUSAL>::C>(p, stream);
-    }
+  if constexpr (!SPLIT && DQK == 64) {
+    if (kind == Kind::kShortWide) return launch_cfg<typename ShortWideInstance<DQK, DV, CAUSAL>::C>(p, stream);
   }
-  if constexpr (SPLIT && DQK != 192) {
-    if (split_short(p)) return launch_cfg<typename ShortInstance<DQK, DV, CAUSAL, true>::C>(p, stream);
+  if constexpr (DQK != 192) {
+    if (kind == Kind::kShort) return launch_cfg<typename ShortInstance<DQK, DV, CAUSAL, SPLIT>::C>(p, stream);
   }
   return launch_cfg<typename Instance<DQK, DV, CAUSAL, SPLIT>::C>(p, stream);
 }
 
 template <bool SPLIT>
 hipError_t launch_dims(FwdParams p, int d_qk, int d_v, bool causal, hipStream_t stream) {
-  const Kind sh = SPLIT ? Kind::kLong : pick_launch(p, d_qk, d_v, causal);
+  const Kind sh = launch_kind(p, d_qk, d_v, causal, SPLIT);
   if (d_qk == 64 && d_v == 64)
     return causal ? launch_instance<64, 64, true, SPLIT>(p, sh, stream)
                   : launch_instance<64, 64, false, SPLIT>(p, sh, stream);
@@ -1342,6 +1345,32 @@ int instance_rows(int batch, int hq, int sq, int d_qk, int d_v, bool causal) {
       return ShortInstance<64, 64, false>::C::BM;
     default:
       return bm;
+  }
+}
+
+int launch_instance_id(int batch, int hq, int hkv, int sq, int sk, int d_qk, int d_v, bool causal, int n_split) {
+  if (block_rows(d_qk, d_v, causal) == 0 || batch <= 0 || hq <= 0 || hkv <= 0 || hq % hkv != 0 || sq <= 0 || sk < 0 ||
+      n_split < 0)
+    return 0;
+  FwdParams p{};
+  p.batch = batch;
+  p.hq = hq;
+  p.hkv = hkv;
+  p.group = hq / hkv;
+  p.sq = sq;
+  p.sk = sk;
+  p.n_split = n_split;
+  switch (launch_kind(p, d_qk, d_v, causal, n_split > 0)) {
+    case Kind::kQuarter:
+      return 1;
+    case Kind::kHalf:
+      return 2;
+    case Kind::kShort:
+      return 3;
+    case Kind::kShortWide:
+      return 4;
+    default:
+      return 5;
   }
 }
 

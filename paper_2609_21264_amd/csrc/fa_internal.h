@@ -50,10 +50,12 @@ struct MergeParams {
 // With a GQA group size divisible by 2 or 4 a workgroup holds as many query heads, each with half or
 // a quarter of these rows.
 int block_rows(int d_qk, int d_v, bool causal);
-// Query rows per block holding one query head of the instance the fused forward runs for this problem:
-// the long instance's block_rows() (256), the short instance's 128 or the key-parts instances' 64 (the
+// Query rows per block holding one query head of the instance that the grid alone selects for the fused
+// forward (a launch with more than twice as many keys as query rows may run another one): the long instance's block_rows() (256), the short instance's 128 or the key-parts instances' 64 (the
 // key quarters run such a block as two workgroups); 0 for unsupported head dimensions or negative sizes.
 int instance_rows(int batch, int hq, int sq, int d_qk, int d_v, bool causal);
+// The instance a launch runs (n_split == 0: the fused forward; else split mode), as fa_instance_t's values.
+int launch_instance_id(int batch, int hq, int hkv, int sq, int sk, int d_qk, int d_v, bool causal, int n_split);
 // Workgroups of the long instance's grid (one part per query block and packed heads).
 int64_t forward_workgroups(int batch, int hq, int hkv, int sq);
 

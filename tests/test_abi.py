@@ -94,6 +94,44 @@ def test_fwd_rows_other_dims(lib):
     assert fa.fa_fwd_rows(1, 1, -64, 64, 64, False) == 0
 
 
+Q_, H_, S_, SW_, L_ = (fa.FA_INSTANCE_QUARTERS, fa.FA_INSTANCE_HALVES, fa.FA_INSTANCE_SHORT,
+                       fa.FA_INSTANCE_SHORT_WIDE, fa.FA_INSTANCE_LONG)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+def test_fwd_instance_square_problems(lib, d, causal):
+    """With as many keys as query rows the instance follows from the grid: the rows fa_fwd_rows reports, the
+    quarters among the key parts up to a 32-row workgroup per compute unit (two for a long enough causal
+    triangle), the 128-key tiles of the short instance from 1024 keys."""
+    for hq in (1, 2, 7, 12, 31, 32, 33, 64, 100, 250, 256, 257, 1000, 1025):
+        for sq in (1, 32, 64, 65, 200, 256, 257, 300, 1023, 1024, 2047, 2048, 5000):
+            rows = fa.fa_fwd_rows(1, hq, sq, d, d, causal)
+            wgs = hq * -(-sq // 32)
+            many = causal and (d == 64 or sq >= 2048)
+            quarters = sq > (64 if d == 64 else 256) and wgs <= (512 if many else 256)
+            expected = {64: Q_ if quarters else H_, 128: SW_ if d == 64 and sq >= 1024 else S_, 256: L_}[rows]
+            assert fa.fa_fwd_instance(1, hq, hq, sq, sq, d, d, causal) == expected, (hq, sq)
+
+
+def test_fwd_instance_split_mode(lib):
+    # blocks of 128 row-heads where they pad fewer rows, or where blocks of 256 leave compute units idle
+    assert fa.fa_fwd_instance(1, 28, 4, 100, 20001, 128, 128, True, 18) == S_
+    assert fa.fa_fwd_instance(1, 32, 8, 64, 32768, 128, 128, True, 16) == S_
+    assert fa.fa_fwd_instance(1, 32, 8, 100, 32768, 128, 128, True, 16) == L_
+    assert fa.fa_fwd_instance(1, 32, 8, 64, 32768, 128, 128, True, 64) == L_
+    assert fa.fa_fwd_instance(1, 4, 4, 1, 3000, 192, 128, True, 8) == L_
+
+
+def test_fwd_instance_other_sizes(lib):
+    assert fa.fa_fwd_instance(1, 1, 1, 64, 64, 192, 128, True) == L_
+    assert fa.fa_fwd_instance(1, 1, 1, 64, 0, 128, 128, True) == H_
+    for args in ((1, 1, 1, 64, 64, 96, 96, True), (1, 1, 1, 64, 64, 128, 64, False), (0, 1, 1, 64, 64, 64, 64, True),
+                 (1, 0, 0, 64, 64, 64, 64, True), (1, 4, 3, 64, 64, 64, 64, True), (1, 4, 0, 64, 64, 64, 64, True),
+                 (1, 4, 4, 0, 64, 64, 64, True), (1, 4, 4, 64, -1, 64, 64, True), (1, 4, 4, 64, 64, 64, 64, True, -1)):
+        assert fa.fa_fwd_instance(*args) == fa.FA_INSTANCE_NONE, args
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(B=-1), fa.FA_ERR_BAD_SHAPE),
     (dict(Hq=-4), fa.FA_ERR_BAD_SHAPE),
