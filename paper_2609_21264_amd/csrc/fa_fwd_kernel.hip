@@ -1094,6 +1094,8 @@ struct QuarterInstance {
   using C = Cfg<DQK, DV, 128, 4, 1, CAUSAL, false, DQK >= 128 ? 1 : 2, 2, DQK >= 128 ? 2 : 4, 2, 3, 4>;
 };
 
+constexpr int64_t kCus = 256;  // compute units of MI355X
+
 // Whether a problem of the key-halves instance runs the quarters: its 32-row workgroups are at most one
 // per CU. Measured against the halves (interleaved, one box): d = 64 one head S256 5.15 -> 4.62 us, H12
 // S512 causal 6.48 -> 5.37, H8 S1024 9.1 -> 6.8, 16/2 100 x 16384 97 -> 57; d = 128 H8 S1024 12.3 -> 10.6,
@@ -1104,7 +1106,6 @@ struct QuarterInstance {
 // (512 workgroups at S1024 0.83x). Up to 64 keys at d = 64 (0.92x) and 256 at d = 128 (0.85-1.00x) the
 // four-way merge costs more than the one or two steps saved.
 bool key_quarters(const FwdParams& p, int d_qk, bool causal) {
-  constexpr int64_t kCus = 256;
   const int64_t wgs = (int64_t)p.batch * p.hq * ((p.sq + 31) / 32);
   const bool triangle = causal && (int64_t)p.sq * 2 >= p.sk;
   if (d_qk == 64) return p.sk > 64 && wgs <= (triangle ? 2 * kCus : kCus);
@@ -1138,30 +1139,72 @@ Kind pick_instance(const FwdParams& p, int d_qk, int d_v, bool causal) {
   return blocks <= (d_qk == 64 ? kShortMaxBlocks64 : kShortMaxBlocks128) ? Kind::kShort : Kind::kLong;
 }
 
-// The instance a launch runs: pick_instance, except where the keys are more than twice the query rows (a
-// chunk of a prompt against its cache). Such a grid is flat, all its chains are about equally long with or
-// without the mask, so what a causal triangle gains from small blocks (a shorter longest chain) is not
-// there. Measured (interleaved, one box), pick_instance's choice against this one: d = 128 causal 32/8
-// 1500 x 9000 (192 blocks, halves) 207.9 -> 194.2 us, 20 heads 2000 x 20000 (160) 483 -> 402, 32 heads
-// 1700 x 12000 (224, short) 302 -> 287, without a mask 16 heads 2560 x 8000 (160) 179 -> 161, 32 heads
-// 1900 x 6000 (256) 174 -> 165; at 128 blocks and fewer the halves stay ahead (32/8 1024 x 16384 249
-// against 269 and 316). d = 64 causal, halves against short: 16 heads 4000 x 16000 (256) 268 -> 246, B2
-// H12 2500 x 10000 (240) 170 -> 151; at 168 blocks (28/4 1300 x 5000) 60 against 67.
-constexpr int64_t kFlatLong128 = 160, kFlatHalf64 = 200;
-Kind pick_launch(const FwdParams& p, int d_qk, int d_v, bool causal) {
-  const Kind kind = pick_instance(p, d_qk, d_v, causal);
-  if (kind == Kind::kLong || p.sk <= (int64_t)p.sq * 2) return kind;
-  const int64_t blocks = (int64_t)p.batch * p.hq * ((p.sq + 255) / 256);
-  if (d_qk == 128) return blocks >= kFlatLong128 ? Kind::kLong : kind;
-  return kind == Kind::kHalf && blocks > kFlatHalf64 ? Kind::kShort : kind;
-}
-
 // log2 of the query heads a workgroup of `nwaves` waves packs: 4, 2 or 1 heads, the largest that
 // divides the GQA group size (and the wave count).
 int packed_heads_log2(int group, int nwaves) {
   if (group % 4 == 0 && nwaves % 4 == 0) return 2;
   if (group % 2 == 0 && nwaves % 2 == 0) return 1;
   return 0;
+}
+
+// Workgroups and padded query rows per head of an instance whose workgroups hold `rowheads` row-heads in
+// `rwaves` waves with rows of their own (launch_cfg's decomposition).
+struct Grid {
+  int64_t wgs, rows;
+};
+Grid grid_of(const FwdParams& p, int rowheads, int rwaves) {
+  const int hw_log = packed_heads_log2(p.group, rwaves);
+  const int64_t rows = rowheads >> hw_log, blocks = (p.sq + rows - 1) / rows;
+  return {(int64_t)p.batch * p.hkv * (p.group >> hw_log) * blocks, blocks * rows};
+}
+
+// pick_instance, except where the keys are more than twice the query rows (a chunk of a prompt against its
+// cache). Such a grid is flat, its chains are about equally long with or without the mask, so what a causal
+// triangle gains from small blocks (a shorter longest chain) is not there, and blocks with more rows read
+// each K/V fragment for more of them. That pays only where the larger blocks still fill the chip and pad no
+// more rows, so the rule counts the workgroups and padded rows that each instance would launch (the blocks
+// of pick_instance count neither a GQA group's packing nor padding). Measured over 530 random shapes of 160
+// to 256 blocks at d = 128 and 201 to 320 at d = 64, each in every instance (us, interleaved, one box):
+//  * d = 128, the short instance's grid exceeds a workgroup per CU: from the halves (causal, up to 192
+//    blocks) to the short instance, unless it pads over a seventh more rows: 8/8 8 x 537 x 3786 0.84x the
+//    time, 16/16 4 x 550 x 17276 0.73x, 15/5 4 x 706 x 2486 0.93x; at 1.2 times the rows 32/32 3 x 299 x
+//    2260 1.27x. At or below a workgroup per CU it leaves CUs idle: 32/8 5 x 61 x 12957 1.17x.
+//  * d = 128, on to the long instance where that pads at most an eighth more rows again and the grid is
+//    flat enough (no mask, or six times as many keys): 20 heads 2000 x 20000 483 -> 402, 32/8 1500 x 9000
+//    208 -> 194, 16/16 16 x 229 x 3760 196 -> 120, without a mask 16 heads 2560 x 8000 179 -> 161. With more
+//    padding it is slower (28/4 2 x 777 x 5001, 1024 rows for 896: 118.5 against 114.5 in the short
+//    instance, 64/16 3 x 154 x 5481 1.20x), with fewer keys per row too (64/8 770 x 3013 1.05x), and with
+//    idle CUs most of all (B4 64/8 1 x 3454, a grid of 64: 1.29x, 35/5 5 x 1 x 358: 2.3x). Grids without a
+//    mask are flat with fewer keys as well (9 heads 5000 x 5000 123 against 112 in the long instance, 24
+//    heads 2048 x 2048 55.5 against 51.9); they stay with the grid's choice.
+//  * d = 64 (causal, halves): to the short instance where its grid takes one and a half to two workgroups
+//    per CU and it pads at most a tenth more rows, a fifth from seven quarters per CU on: 16 heads 4000 x
+//    16000 268 -> 246, 12 heads 2 x 2500 x 10000 170 -> 151, 9/9 4 x 1363 x 31199 0.71x, 5/5 32 x 303 x
+//    11131 (1.2 times the rows, 480 workgroups) 0.66x; at 1.11 times the rows in 400 workgroups 16/16 5 x
+//    528 x 6548 1.09x, at 4/3 1.10-1.21x, grids of 257 to 384 1.00-1.13x, above 512 0.84-1.11x. Of
+//    at most a workgroup per CU: where the halves need more than that (16/2 16 x 73 x 22765 0.80x, 56/8 4 x
+//    76 x 1996 0.95x), or K and V are too large to be read twice as often (above 80 MiB: 32/8 8 x 51 x 27897
+//    0.75x, 8/8 32 x 42 x 6307 0.85x; below, 32/8 8 x 48 x 588 1.13x). Problems of the key quarters stay
+//    there (the short instance 1.3-1.9x).
+constexpr int64_t kFlatMin128 = 160, kFlatMin64 = 201;  // blocks
+Kind pick_launch(const FwdParams& p, int d_qk, int d_v, bool causal) {
+  const Kind kind = pick_instance(p, d_qk, d_v, causal);
+  if (kind == Kind::kLong || p.sk <= (int64_t)p.sq * 2) return kind;
+  const int64_t blocks = (int64_t)p.batch * p.hq * ((p.sq + 255) / 256);
+  if (blocks < (d_qk == 128 ? kFlatMin128 : kFlatMin64)) return kind;
+  const Grid lng = grid_of(p, 256, 4), sht = grid_of(p, 128, 4), hlf = grid_of(p, 64, 2);
+  if (d_qk == 128) {
+    if (sht.wgs <= kCus || (kind == Kind::kHalf && 7 * sht.rows > 8 * hlf.rows)) return kind;
+    const bool flat = !causal || p.sk >= (int64_t)p.sq * 6;
+    return flat && 8 * lng.rows <= 9 * sht.rows ? Kind::kLong : Kind::kShort;
+  }
+  if (kind != Kind::kHalf || key_quarters(p, d_qk, causal)) return kind;
+  const bool short_fits = 10 * sht.rows <= (4 * sht.wgs >= 7 * kCus ? 12 : 11) * hlf.rows;
+  if (sht.wgs <= kCus) {
+    const bool large_kv = 2.0 * p.batch * p.hkv * p.sk * (d_qk + d_v) > 80.0 * (1 << 20);
+    return (short_fits && hlf.wgs > kCus) || large_kv ? Kind::kShort : kind;
+  }
+  return short_fits && 2 * sht.wgs > 3 * kCus && sht.wgs <= 2 * kCus ? Kind::kShort : kind;
 }
 
 template <class C>
@@ -1219,13 +1262,9 @@ hipError_t launch_cfg(FwdParams p, hipStream_t stream) {
 // -> 14.5. With equal padding on a full grid the long instance reads each fragment for twice the rows:
 // 32/8 100 x 32768 75.3 against 78.8, 8/1 500 x 131072 253 against 274.
 bool split_short(const FwdParams& p) {
-  constexpr int64_t kCus = 256;
-  const int hw_log = packed_heads_log2(p.group, 4);
-  const int64_t rows_long = 256 >> hw_log, rows_short = 128 >> hw_log;
-  const int64_t blocks_long = (p.sq + rows_long - 1) / rows_long, blocks_short = (p.sq + rows_short - 1) / rows_short;
-  const int64_t heads = (int64_t)p.batch * p.hkv * (p.group >> hw_log);
-  if (heads * blocks_short * p.n_split > INT32_MAX) return false;
-  return blocks_short * rows_short < blocks_long * rows_long || heads * blocks_long * p.n_split < kCus;
+  const Grid lng = grid_of(p, 256, 4), sht = grid_of(p, 128, 4);
+  if (sht.wgs * p.n_split > INT32_MAX) return false;
+  return sht.rows < lng.rows || lng.wgs * p.n_split < kCus;
 }
 
 // The instance a launch runs (every kind, and split mode's own choice).

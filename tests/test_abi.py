@@ -114,6 +114,46 @@ def test_fwd_instance_square_problems(lib, d, causal):
             assert fa.fa_fwd_instance(1, hq, hq, sq, sq, d, d, causal) == expected, (hq, sq)
 
 
+# More than twice as many keys as query rows: the instance that measured fastest, or level with it. Where the
+# larger blocks of the short and long instances would leave compute units idle or be mostly padding, the
+# problem stays with what its grid selects.
+FLAT = [
+    # (B, Hq, Hkv, Sq, Sk, d, causal, instance)
+    (5, 32, 8, 64, 12957, 128, True, H_),     # 40 long or 80 short workgroups: idle compute units
+    (5, 32, 8, 28, 11986, 128, True, Q_),
+    (5, 35, 5, 1, 358, 128, True, Q_),
+    (4, 64, 8, 1, 3454, 128, True, S_),       # 64 long workgroups
+    (1, 256, 32, 43, 802, 128, True, S_),
+    (3, 32, 32, 299, 2260, 128, True, H_),    # 320 rows padded to 384 and 512
+    (2, 28, 4, 777, 5001, 128, True, S_),     # 896 against 1024
+    (1, 64, 8, 770, 3013, 128, True, S_),     # 3.9 times as many keys: not flat enough under a mask
+    (8, 8, 8, 537, 3786, 128, True, S_),
+    (4, 15, 5, 706, 2486, 128, True, S_),
+    (1, 32, 8, 1500, 9000, 128, True, L_),
+    (1, 20, 20, 2000, 20000, 128, True, L_),
+    (16, 16, 16, 229, 3760, 128, True, L_),
+    (1, 16, 16, 2560, 8000, 128, False, L_),
+    (1, 32, 32, 1900, 6000, 128, False, L_),
+    (1, 9, 9, 5000, 10000, 128, False, S_),   # exactly twice: the grid's choice
+    (1, 32, 8, 1024, 16384, 128, True, H_),   # 128 blocks
+    (8, 32, 4, 6, 790, 64, True, Q_),
+    (1, 28, 4, 1300, 5000, 64, True, H_),     # 168 blocks
+    (8, 32, 8, 48, 588, 64, True, H_),        # 128 short workgroups, K and V fit the caches
+    (8, 32, 8, 51, 27897, 64, True, SW_),     # they do not
+    (16, 16, 2, 73, 22765, 64, True, SW_),    # 384 workgroups of halves, 192 of the short instance
+    (5, 16, 16, 528, 6548, 64, True, H_),     # 400 short workgroups at 640 rows for 576
+    (32, 5, 5, 303, 11131, 64, True, SW_),    # 480 at 384 for 320
+    (8, 32, 32, 152, 7225, 64, True, H_),     # 512 at 256 for 192
+    (1, 16, 16, 4000, 16000, 64, True, SW_),
+    (2, 12, 12, 2500, 10000, 64, True, SW_),
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Sk,d,causal,instance", FLAT)
+def test_fwd_instance_chunks_against_a_longer_cache(lib, B, Hq, Hkv, Sq, Sk, d, causal, instance):
+    assert fa.fa_fwd_instance(B, Hq, Hkv, Sq, Sk, d, d, causal) == instance
+
+
 def test_fwd_instance_split_mode(lib):
     # blocks of 128 row-heads where they pad fewer rows, or where blocks of 256 leave compute units idle
     assert fa.fa_fwd_instance(1, 28, 4, 100, 20001, 128, 128, True, 18) == S_

@@ -78,7 +78,7 @@ def big():
 @pytest.mark.parametrize("causal", [False, True], ids=["full", "causal"])
 def test_fused_at_largest_key_length(big, causal):
     sq, q, k, v = big
-    assert fa.fa_fwd_rows(1, q.shape[1], sq, D, D, causal) == 64
+    assert fa.fa_fwd_instance(1, q.shape[1], 2, sq, MAX_SK, D, D, causal) == fa.FA_INSTANCE_QUARTERS
     o, lse = fa.forward(q, k, v, causal=causal, scale=SCALE, return_lse=True)
     torch.cuda.synchronize()
     check(o, lse, sq, MAX_SK, causal, f"fused causal={causal}")
@@ -90,7 +90,7 @@ def test_fused_long_instance_at_largest_key_length(big, causal):
     instances take, so the long instance's loaders address the end of the 4 GiB heads."""
     sq, _, k, v = big
     group = 129
-    assert fa.fa_fwd_rows(1, 2 * group, sq, D, D, causal) == 256
+    assert fa.fa_fwd_instance(1, 2 * group, 2, sq, MAX_SK, D, D, causal) == fa.FA_INSTANCE_LONG
     q = torch.zeros(1, 2 * group, sq, D, dtype=torch.bfloat16, device="cuda")
     q[..., 0] = 1.0
     o, lse = fa.forward(q, k, v, causal=causal, scale=SCALE, return_lse=True)
@@ -99,11 +99,11 @@ def test_fused_long_instance_at_largest_key_length(big, causal):
 
 
 def test_fused_short_instance_at_largest_key_length(big):
-    """100 query heads per key/value head without a mask: 200 query blocks, which the short instance
-    runs (causal problems at this head dimension go from the key-halves to the long instance)."""
+    """100 query heads per key/value head without a mask: 200 query blocks in 50 workgroups, which stay with
+    the short instance also against this many keys."""
     sq, _, k, v = big
     group = 100
-    assert fa.fa_fwd_rows(1, 2 * group, sq, D, D, False) == 128
+    assert fa.fa_fwd_instance(1, 2 * group, 2, sq, MAX_SK, D, D, False) == fa.FA_INSTANCE_SHORT
     q = torch.zeros(1, 2 * group, sq, D, dtype=torch.bfloat16, device="cuda")
     q[..., 0] = 1.0
     o, lse = fa.forward(q, k, v, causal=False, scale=SCALE, return_lse=True)
@@ -112,11 +112,11 @@ def test_fused_short_instance_at_largest_key_length(big):
 
 
 def test_fused_short_instance_at_largest_key_length_below_160_blocks(big):
-    """75 query heads per key/value head without a mask: 150 query blocks, which the short instance runs
-    also with more than twice as many keys as query rows (from 160 blocks those run the long one)."""
+    """75 query heads per key/value head without a mask: 150 query blocks, below the 160 from which the rule
+    for chunks against a longer cache looks at the grid, and no packed heads."""
     sq, _, k, v = big
     group = 75
-    assert fa.fa_fwd_rows(1, 2 * group, sq, D, D, False) == 128
+    assert fa.fa_fwd_instance(1, 2 * group, 2, sq, MAX_SK, D, D, False) == fa.FA_INSTANCE_SHORT
     q = torch.zeros(1, 2 * group, sq, D, dtype=torch.bfloat16, device="cuda")
     q[..., 0] = 1.0
     o, lse = fa.forward(q, k, v, causal=False, scale=SCALE, return_lse=True)
