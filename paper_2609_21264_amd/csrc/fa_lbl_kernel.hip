@@ -113,6 +113,14 @@ __device__ __forceinline__ void block_barrier() {
 //    non-temporal stores alone 148 and 270, the sweeps alone 195 and 297, neither 212 and 454.
 constexpr int kScoreThreads = (kWaves + 1) * 64;
 
+// Tile (of nt > 0) at which block qb of head bh starts its staggered key sweep. Unsigned: bh goes up to the
+// largest int. (A signed product would not be a constant expression below.)
+constexpr __host__ __device__ int sweep_start(int bh, int qb, int nt) {
+  return (int)(((unsigned)bh * 37u + (unsigned)qb * 11u) % (unsigned)nt);
+}
+static_assert(sweep_start(INT32_MAX, 0, 7) < 7 && sweep_start(INT32_MAX, 0, 7) >= 0, "no signed overflow");
+static_assert(sweep_start(3, 5, 100) == (3 * 37 + 5 * 11) % 100, "");
+
 template <int DQK, bool STREAM>
 __global__ __launch_bounds__(kScoreThreads) void lbl_scores_kernel(LblParams p) {
   constexpr int KS = DQK / 16;                          // k-steps of the product
@@ -138,7 +146,7 @@ __global__ __launch_bounds__(kScoreThreads) void lbl_scores_kernel(LblParams p) 
   const int rows_here = min(kLblRows, p.sq - qb * kLblRows);
   auto kslot = [&](int t) { return smem + (t % NKR) * K_BYTES; };
   // Key tile of step j: the sweep starts at tile `first` and wraps (steps from nt on load nothing).
-  const int first = STREAM && nt > 0 ? (int)((unsigned)(bh * 37 + qb * 11) % (unsigned)nt) : 0;
+  const int first = STREAM && nt > 0 ? sweep_start(bh, qb, nt) : 0;
   auto tile = [&](int j) { return !STREAM || j >= nt ? j : j + first >= nt ? j + first - nt : j + first; };
   if (wave == kWaves) {
     // The loads go K0 .. K(D-1), then per step j: K(j+D). Before step j, K(j) must have landed; issued
