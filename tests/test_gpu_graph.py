@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
 
 # name: (B, Hq, Hkv, Sq, Sk, d_qk, d_v, causal, call)
 CASES = {
-    # a few query blocks: the key-halves instance
+    # a few query blocks: the key quarters; 96 of them in 480 32-row workgroups: the key halves
+    "fused-halves": (1, 48, 24, 300, 300, 128, 128, True,
+                     lambda q, k, v, c: fa.forward(q, k, v, causal=c, return_lse=True)),
     "fused": (1, 4, 2, 300, 300, 128, 128, True, lambda q, k, v, c: fa.forward(q, k, v, causal=c, return_lse=True)),
     # 96 blocks of 256 rows at d = 64 without a mask: the short instance
     "fused-short": (1, 96, 48, 130, 200, 64, 64, False,
@@ -31,6 +33,8 @@ CASES = {
                    lambda q, k, v, c: fa.forward(q, k, v, causal=c, return_lse=True)),
     "split": (1, 4, 1, 64, 2000, 128, 128, True,
               lambda q, k, v, c: fa.forward(q, k, v, causal=c, return_lse=True, n_split=4)),
+    "decode-one-part": (2, 8, 2, 2, 300, 128, 128, True,
+                        lambda q, k, v, c: fa.forward(q, k, v, causal=c, return_lse=True, decode=True, n_split=1)),
     "decode": (2, 8, 2, 2, 3000, 128, 128, True,
                lambda q, k, v, c: fa.forward(q, k, v, causal=c, return_lse=True, decode=True, n_split="auto")),
     "unfused": (1, 2, 1, 200, 300, 64, 64, True,
@@ -45,15 +49,15 @@ def inputs(case, seed):
     return W.make_inputs(w)
 
 
-INSTANCE = {"fused": 64, "fused-short": 128, "fused-long": 256, "fused-d192": 256}
+INSTANCE = {"fused": fa.FA_INSTANCE_QUARTERS, "fused-halves": fa.FA_INSTANCE_HALVES,
+            "fused-short": fa.FA_INSTANCE_SHORT, "fused-long": fa.FA_INSTANCE_LONG, "fused-d192": fa.FA_INSTANCE_LONG}
 
 
 @pytest.mark.parametrize("case", list(CASES))
 def test_graph_replay_matches_eager(case):
     causal, call = CASES[case][7], CASES[case][8]
     if case in INSTANCE:
-        B, Hq, _, Sq, _, dqk, dv, _, _ = CASES[case]
-        assert fa.fa_fwd_rows(B, Hq, Sq, dqk, dv, causal) == INSTANCE[case]
+        assert fa.fa_fwd_instance(*CASES[case][:7], causal) == INSTANCE[case]
     sets = [inputs(case, 7100), inputs(case, 7200)]
     q, k, v = (t.cuda() for t in sets[0])
 

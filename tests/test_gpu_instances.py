@@ -1,12 +1,11 @@
-"""GPU parity of the three instances of the fused kernel.
+"""GPU parity of the instances of the fused kernel.
 
-Which instance runs follows from the grid alone, and the library reports it (fa_fwd_rows, the query
-rows of one head per workgroup): the key-halves instance (64) for the smallest grids, the short
-instance (128) for mid-sized ones, and the long instance (256) for the rest and for every
-d_qk = 192 problem. The small edge cases of test_gpu_parity.py have
-few blocks, so they run the instance of the smallest grids; here the same cases are widened (more
-heads, same per-head shape and GQA ratio, seeded afresh) until each other instance runs them, and
-every output element is compared with the fp64 oracle.
+Which instance runs follows from the sizes, and the library reports it (fa_fwd_instance): the key parts
+for the smallest grids (quarters while 32-row workgroups leave compute units idle, halves above), the
+short instance for mid-sized ones, and the long instance for the rest and for every d_qk = 192 problem.
+The small edge cases of test_gpu_parity.py have few blocks, so they run the key parts; here the same
+cases are widened (more heads, same per-head shape and GQA ratio, seeded afresh) until the halves, the
+short and the long instance run them, and every output element is compared with the fp64 oracle.
 """
 
 import numpy as np
@@ -21,12 +20,15 @@ from test_gpu_parity import SMALL_CASES
 
 pytestmark = pytest.mark.gpu
 
-HALF, SHORT, LONG = 64, 128, 256  # rows per workgroup of one head, by instance
-NAMES = {HALF: "halves", SHORT: "short", LONG: "long"}
+QUARTER, HALF, SHORT, LONG = (fa.FA_INSTANCE_QUARTERS, fa.FA_INSTANCE_HALVES, fa.FA_INSTANCE_SHORT,
+                              fa.FA_INSTANCE_LONG)
+NAMES = {QUARTER: "quarters", HALF: "halves", SHORT: "short", LONG: "long"}
 
 
-def rows(w):
-    return fa.fa_fwd_rows(w.B, w.Hq, w.Sq, w.dqk, w.dv, w.causal)
+def instance(w):
+    """The instance `w` runs, either tile width of the short one as SHORT."""
+    i = fa.fa_fwd_instance(w.B, w.Hq, w.Hkv, w.Sq, w.Sk, w.dqk, w.dv, w.causal)
+    return SHORT if i == fa.FA_INSTANCE_SHORT_WIDE else i
 
 
 def blocks(w):
@@ -34,27 +36,26 @@ def blocks(w):
 
 
 def widened(w, target):
-    """The same per-head problem with the fewest multiples of its heads that run the instance of
-    `target` rows, or None if no head count does (the instances follow each other as the grid grows:
-    key halves, short, long)."""
-    for m in range(1, 8192):
+    """The same per-head problem with the fewest multiples of its heads that run the instance `target`, or
+    None if no head count does."""
+    for m in range(1, 2049):
         v = w.with_(Hq=w.Hq * m, Hkv=w.Hkv * m)
-        r = rows(v)
-        if r == target:
+        if instance(v) == target:
             return v.with_(name=w.name + f" x{m} heads", seed=w.seed + 500 + target)
-        if r > target:
-            return None
     return None
 
 
 CASES = [w for w in SMALL_CASES if (w.dqk, w.dv) != (192, 128)]
-WIDE = [(w, t) for w in CASES for t in (SHORT, LONG)]
+# the halves too where the case itself runs the quarters and more heads of it run the halves (without a mask
+# at d = 64 they take longer sequences than these: test_gpu_key_parts.py)
+WIDE = [(w, t) for w in CASES for t in (HALF, SHORT, LONG)
+        if t != HALF or (instance(w) == QUARTER and widened(w, HALF) is not None)]
 
 
-def test_small_cases_run_the_key_halves_instance():
+def test_small_cases_run_the_key_parts():
     # the premise of this file: the edge cases of test_gpu_parity.py have few blocks
-    assert CASES and all(rows(w) == HALF for w in CASES)
-    assert all(rows(w) == LONG for w in SMALL_CASES if w.dqk == 192)
+    assert CASES and all(instance(w) in (QUARTER, HALF) for w in CASES)
+    assert all(instance(w) == LONG for w in SMALL_CASES if w.dqk == 192)
 
 
 @pytest.mark.parametrize("w,target", WIDE, ids=[f"{w.name}-{NAMES[t]}" for w, t in WIDE])
@@ -65,17 +66,11 @@ def test_wider_instances_small_shapes_match_oracle(w, target):
 
 
 def _heads_for(make, target):
-    """The smallest even head count whose problem `make(heads)` runs the instance of `target` rows."""
-    for heads in range(2, 8192, 2):
-        r = rows(make(heads))
-        if r == target:
-            return heads
-        if r > target:
-            return None
-    return None
+    """The smallest even head count whose problem `make(heads)` runs the instance `target`."""
+    return next((heads for heads in range(2, 4096, 2) if instance(make(heads)) == target), None)
 
 
-SPIKES = [(c, t) for c in (False, True) for t in (HALF, SHORT, LONG)]
+SPIKES = [(c, t) for c in (False, True) for t in (QUARTER, HALF, SHORT, LONG)]
 
 
 @pytest.mark.parametrize("causal,target", SPIKES,
@@ -97,7 +92,7 @@ def test_rising_maxima_rebase_every_instance(causal, target):
     compare(to_f64(o), lse.cpu().double().numpy(), o_ref, lse_ref, w.name)
 
 
-ROW0 = [(d, t) for d in (64, 128) for t in (HALF, SHORT, LONG)]
+ROW0 = [(d, t) for d in (64, 128) for t in (QUARTER, HALF, SHORT, LONG)]
 
 
 @pytest.mark.parametrize("d,target", ROW0, ids=[f"d{d}-{NAMES[t]}" for d, t in ROW0])
@@ -116,10 +111,10 @@ def test_causal_first_row_bitwise_every_instance(d, target):
 
 @pytest.mark.parametrize("cfg", [1, 2])
 def test_small_benchmark_configs_second_seed(cfg):
-    # configs 1 (one block: key halves) and 2 (384 blocks: short); test_gpu_parity checks them in
+    # configs 1 (one block: key quarters) and 2 (384 blocks: short); test_gpu_parity checks them in
     # full, and here on a second seed
     w = W.CONFIGS[cfg]
-    assert rows(w) == (HALF if cfg == 1 else SHORT)
+    assert instance(w) == (QUARTER if cfg == 1 else SHORT)
     check_full(w.with_(seed=w.seed + 700))
 
 
@@ -138,8 +133,8 @@ def test_instance_boundary(d, causal, heads):
     w = make(heads)
     assert blocks(w) == heads
     last = heads if (d, causal, heads) in SWITCHES else heads - 1
-    assert rows(make(last + 1)) > rows(make(last))
-    print(f"\n[case] {w} ({NAMES[rows(w)]})", flush=True)
+    assert instance(make(last + 1)) > instance(make(last))  # in the order in which the grid grows
+    print(f"\n[case] {w} ({NAMES[instance(w)]})", flush=True)
     check_full(w)
 
 
@@ -163,7 +158,7 @@ WIDE_TILES = [
 
 @pytest.mark.parametrize("w", WIDE_TILES, ids=[w.name for w in WIDE_TILES])
 def test_short_instance_wide_tiles_match_oracle(w):
-    assert rows(w) == SHORT and w.Sk >= 1024
+    assert fa.fa_fwd_instance(w.B, w.Hq, w.Hkv, w.Sq, w.Sk, 64, 64, w.causal) == fa.FA_INSTANCE_SHORT_WIDE
     print(f"\n[case] {w}", flush=True)
     q, k, v = W.make_inputs(w)
     o, lse = run_gpu(q, k, v, w)
@@ -178,7 +173,7 @@ def test_short_instance_wide_tiles_match_oracle(w):
 def test_short_instance_wide_tiles_rebase(causal):
     """Rising maxima (keys scaled x4 .. x32 in four tiles of 128 keys) through the 128-key tiles."""
     w = _wide("spikes", 330 if causal else 80, 110 if causal else 40, 64, 1500, causal, 309)
-    assert rows(w) == SHORT
+    assert fa.fa_fwd_instance(w.B, w.Hq, w.Hkv, w.Sq, w.Sk, 64, 64, causal) == fa.FA_INSTANCE_SHORT_WIDE
     q, k, v = W.make_inputs(w)
     for key, factor in ((70, 4.0), (300, 8.0), (900, 16.0), (1490, 32.0)):
         k[:, :, key] *= factor

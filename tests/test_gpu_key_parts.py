@@ -30,6 +30,10 @@ CASES = [
     _w("scale 0", 64, 2, 2, 70, 300, False, scale=0.0),
     _w("negative scale", 128, 7, 1, 70, 700, True, scale=-0.07),
     _w("sigma 2", 64, 5, 5, 130, 640, True, sigma=2.0),
+    # halves without a mask
+    _w("halves", 64, 60, 15, 250, 257, False),
+    _w("halves scale 0", 64, 60, 60, 200, 130, False, scale=0.0),
+    _w("halves sigma 2", 64, 62, 31, 224, 321, False, sigma=2.0),
     # the last grid of quarters and the first of halves
     *[_w("switch", 64, h, h, 256, 300, False) for h in (32, 33)],
     *[_w("switch", 64, h, h, 200, 200, True) for h in (73, 74)],
@@ -43,12 +47,23 @@ CASES = [
 ]
 
 
+def _instance(w):
+    return fa.fa_fwd_instance(w.B, w.Hq, w.Hkv, w.Sq, w.Sk, w.dqk, w.dv, w.causal)
+
+
+def expected_instance(w):
+    if w.name.startswith("long"):
+        return fa.FA_INSTANCE_LONG
+    halves = w.name.startswith("halves") or (w.name.startswith("switch") and w.Hq in (33, 74, 129, 15))
+    return fa.FA_INSTANCE_HALVES if halves else fa.FA_INSTANCE_QUARTERS
+
+
 @pytest.mark.parametrize("spiked", [False, True], ids=["plain", "rising"])
 @pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
 def test_key_parts_match_oracle(w, spiked):
     """"rising": keys scaled x4 .. x16 a third, two thirds and all the way through, so that parts redo a
     tile from its exact maximum and the parts' references differ widely."""
-    assert fa.fa_fwd_rows(w.B, w.Hq, w.Sq, w.dqk, w.dv, w.causal) == (256 if w.name.startswith("long") else 64)
+    assert _instance(w) == expected_instance(w)
     q, k, v = W.make_inputs(w)
     if spiked:
         for key, factor in ((w.Sk // 3, 4.0), (2 * w.Sk // 3, 8.0), (w.Sk - 1, 16.0)):
@@ -75,7 +90,7 @@ CHUNKED = [
 
 @pytest.mark.parametrize("w", CHUNKED, ids=[w.name for w in CHUNKED])
 def test_head_chunks_match_oracle(w):
-    assert fa.fa_fwd_rows(w.B, w.Hq, w.Sq, w.dqk, w.dv, w.causal) == 256
+    assert _instance(w) == fa.FA_INSTANCE_LONG
     q, k, v = W.make_inputs(w)
     print(f"\n[case] {w}", flush=True)
     o, lse = run_gpu(q, k, v, w)

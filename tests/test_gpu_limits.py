@@ -8,8 +8,8 @@ key/value head h, V = a except V[L] = b. A query row that sees the keys 0 .. n-1
 and LSE = ln n; a row that also sees key L gets O = (L a + e^s b) / (L + e^s) and LSE = ln(L + e^s).
 The last key's score sits far above the others, so the fused kernel's online softmax must rebase on
 the last tile. Two query heads share each key/value head (grouped-query attention), which runs the
-key-halves kernel instance; further fused runs with 100 and 129 per key/value head have enough query
-blocks for the short (without a mask) and the long instance.
+key quarters; further fused runs have enough query heads per key/value head for the key halves, the short
+(without a mask) and the long instance.
 """
 
 import math
@@ -96,6 +96,18 @@ def test_fused_long_instance_at_largest_key_length(big, causal):
     o, lse = fa.forward(q, k, v, causal=causal, scale=SCALE, return_lse=True)
     torch.cuda.synchronize()
     check(o, lse, sq, MAX_SK, causal, f"fused long causal={causal}", group)
+
+
+def test_fused_halves_at_largest_key_length(big):
+    """60 query heads per key/value head and 65 rows: 120 query blocks, in 360 32-row workgroups."""
+    _, _, k, v = big
+    sq, group = 65, 60
+    assert fa.fa_fwd_instance(1, 2 * group, 2, sq, MAX_SK, D, D, False) == fa.FA_INSTANCE_HALVES
+    q = torch.zeros(1, 2 * group, sq, D, dtype=torch.bfloat16, device="cuda")
+    q[..., 0] = 1.0
+    o, lse = fa.forward(q, k, v, causal=False, scale=SCALE, return_lse=True)
+    torch.cuda.synchronize()
+    check(o, lse, sq, MAX_SK, False, "fused halves", group)
 
 
 def test_fused_short_instance_at_largest_key_length(big):

@@ -22,11 +22,20 @@ def _bits(t):
     (2, 14, 14, 2100, 2100, 64, 64, False),
     (1, 56, 8, 2050, 2050, 128, 128, True),
     (1, 24, 24, 1000, 4300, 192, 128, True),
+    # the softmax instances of the shorter rows, and sweeps over few key tiles that start anywhere in them
+    (1, 900, 900, 1000, 100, 64, 64, False),
+    (2, 1000, 125, 301, 300, 64, 64, True),
+    (1, 180, 90, 701, 700, 128, 64, False),
+    (1, 360, 45, 690, 701, 64, 128, True),
+    (1, 40, 40, 1501, 1500, 192, 128, False),
+    (1, 80, 80, 1499, 1497, 64, 64, True),
 ])
 def test_streamed_spill_equals_cached(B, Hq, Hkv, Sq, Sk, dqk, dv, causal):
     """The whole problem in one chunk (its visible scores exceed 160 MiB: streamed) against chunks of one
     group of heads (below it: cached). The operators do the same arithmetic in the same order, so the
     results are the same bits; the cached path is checked against the oracle in test_gpu_lbl."""
+    visible = sum(max(0, min(Sk, i + 1 + Sk - Sq)) if causal else Sk for i in range(Sq)) * 2 * Hq
+    assert B * visible > 160 << 20 and B * Hq * -(-Sq // 128) >= 192 and visible // Hkv < 100 << 20
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
     q, k, v = (torch.randn(s, dtype=torch.bfloat16, device="cuda", generator=g)

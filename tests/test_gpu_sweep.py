@@ -6,7 +6,7 @@ on; this file draws many more combinations of the same parameters at once (head 
 group size, batch, ragged query and key lengths, causal masking, scale and input spread) from a fixed
 seed, so that an interaction nobody thought of still meets the oracle. A quarter of the fused cases
 carry enough heads for the long kernel instance and a fifth enough for the short one (where the head
-dimension and mask have one); the rest are small grids, which run the key-halves instance. A further
+dimension and mask have one); the rest are small grids, which run the key quarters and halves. A further
 set draws d = 64 problems in the short instance's range with 1024-3000 keys, where it takes 128-key
 tiles.
 """
@@ -25,7 +25,7 @@ from parity import compare, rounding_bar, to_f64
 pytestmark = pytest.mark.gpu
 
 DIMS = [(64, 64), (128, 128), (192, 128)]
-# largest grid of 256-row blocks that runs the short instance (by d_qk) and the key-halves instance
+# largest grid of 256-row blocks that runs the short instance (by d_qk) and the key-parts instances
 # (by d_qk and causal masking), as fa_fwd_rows reports; checked against it below
 SHORT_MAX = {64: 1024, 128: 256}
 HALF_MAX = {(64, True): 320, (64, False): 64, (128, True): 192, (128, False): 128}
@@ -51,7 +51,7 @@ def _draw(rng, idx, kind):
         sq = _length(rng, 1, 700)
         sk = sq if rng.uniform() < 0.4 else _length(rng, 1, 700)
         u = rng.uniform()
-        if u < 0.45:  # past the key-halves (u >= 0.25) or the short instance's (u < 0.25) largest grid
+        if u < 0.45:  # past the key parts' (u >= 0.25) or the short instance's (u < 0.25) largest grid
             sq = min(sq, 300)
             sk = min(sk, 300)
             top = SHORT_MAX.get(dqk, 256) if u < 0.25 else HALF_MAX.get((dqk, causal), 0)
@@ -115,11 +115,17 @@ def _rows_model(w):
     return 64 if blocks <= HALF_MAX[(w.dqk, w.causal)] else 128 if blocks <= SHORT_MAX[w.dqk] else 256
 
 
+def _instance(w):
+    return fa.fa_fwd_instance(w.B, w.Hq, w.Hkv, w.Sq, w.Sk, w.dqk, w.dv, w.causal)
+
+
 def test_sweep_draws_every_instance_and_head_dimension():
     rows = [fa.fa_fwd_rows(w.B, w.Hq, w.Sq, w.dqk, w.dv, w.causal) for w in FUSED]
     assert rows == [_rows_model(w) for w in FUSED]
     for d in (64, 128):
         assert {r for r, w in zip(rows, FUSED) if w.dqk == d} == {64, 128, 256}
+        assert {_instance(w) for w in FUSED if w.dqk == d} == {
+            fa.FA_INSTANCE_QUARTERS, fa.FA_INSTANCE_HALVES, fa.FA_INSTANCE_SHORT, fa.FA_INSTANCE_LONG}
     assert {(w.dqk, w.dv) for w in FUSED} == set(DIMS)
     assert len(DECODE) == 48 and all(w.Sq <= 20 for w in DECODE)
 
@@ -131,7 +137,7 @@ def test_fused_sweep(w):
 
 @pytest.mark.parametrize("w", WIDE, ids=[w.name for w in WIDE])
 def test_wide_tile_sweep(w):
-    assert fa.fa_fwd_rows(w.B, w.Hq, w.Sq, w.dqk, w.dv, w.causal) == 128 and w.Sk >= 1024
+    assert _instance(w) == fa.FA_INSTANCE_SHORT_WIDE
     _check(w)
 
 
