@@ -162,6 +162,13 @@ struct TileLoader {
   __device__ __forceinline__ void issue_one(const u32x4& r, uint32_t l, int i) const {
     dma16_buffer<NT>(r, voff[i], l + i * 1024);
   }
+  // Zeros into `slot`, as a tile past the last one loads them: the loads of an empty buffer.
+  __device__ __forceinline__ void issue_zeros(unsigned char* slot, int wave) const {
+    const u32x4 r = {0u, 0u, 0u, 0x00020000u};
+    const uint32_t l = lds(slot, wave);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) issue_one(r, l, i);
+  }
   // Issue all loads of the tile at key n0 into `slot` at once.
   __device__ __forceinline__ void issue(int n0, unsigned char* slot, int wave) const {
     const u32x4 r = rsrc(n0);
