@@ -275,9 +275,10 @@ fa_status_t fa_fwd_unfused(const void* Q, const void* K, const void* V, void* O,
 const char* fa_status_str(fa_status_t s);
 
 /* Query rows per workgroup of the fused kernel's long instance for the given head dimensions when a
- * workgroup holds one query head (256); 0 if unsupported. It runs split mode, every (192, 128)
- * problem, and problems at (d_qk, d_v) = (64, 64) or (128, 128) with more such blocks
- * (B * Hq * ceil(Sq / rows)) than the other instances take (fa_fwd_rows). When Hq / Hkv is divisible
+ * workgroup holds one query head (256); 0 if unsupported. It runs every (192, 128) problem, and at
+ * (d_qk, d_v) = (64, 64) or (128, 128) problems with more such blocks (B * Hq * ceil(Sq / rows)) than
+ * the other instances take (fa_fwd_rows) and split mode where blocks of half the rows would neither pad
+ * fewer rows nor fill more compute units (fa_fwd_instance). When Hq / Hkv is divisible
  * by 2 or 4 a workgroup holds that many query heads of one key/value head with a half or a quarter of
  * these rows each. Host arithmetic only. */
 int fa_block_rows(int d_qk, int d_v, int causal);

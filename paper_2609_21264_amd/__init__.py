@@ -154,8 +154,9 @@ def fa_fwd_unfused(Q: int, K: int, V: int, O: int, LSE: Optional[int], B: int, H
 
 # What a call costs on the host bounds the smallest problems (one head S256 d64: a 4.7 us kernel in a call
 # of 11.9 us, of which the C entry point and its launch are 4.2). So a call on torch's current stream asks
-# for the raw handle only (0.1 us against 2.1 for a Stream object), the device is switched only where it
-# is not the current one (0.3 against 1.4), and the usual case of the checks is one expression.
+# for the raw handle only (0.1 us against 2.1 for a Stream object; the function has no public name in torch,
+# whose compiled graphs call it for the same purpose), the device is switched only where it is not the current
+# one (0.3 against 1.4), and the usual case of the checks is one expression.
 
 def _stream(stream, device):
     """(torch stream, raw handle) for ``stream``. None is torch's current stream of ``device``, given as

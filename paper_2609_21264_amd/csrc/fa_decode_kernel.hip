@@ -276,7 +276,11 @@ hipError_t launch_decode_instance(const DecodeParams& p, hipStream_t stream) {
   // nobody reads again costs bandwidth. Measured against plain loads (interleaved, one box): 512 MiB (128K
   // keys, 32/8 heads) 97.8 -> 84.7 us, 256 MiB (B16, 4099 keys) 51.2 -> 45.5 and (B64, 1025 keys) 52.4 ->
   // 45.6, 150 MiB (B64 64/8, 600 keys) 30.9 -> 29.3; at 128 MiB 27.5 -> 26.4 (d = 128) and 22.1 -> 23.0
-  // (d = 64), at 64 MiB level, below (59 MiB, d = 64) 16.1 -> 17.0.
+  // (d = 64), at 64 MiB level, below (59 MiB, d = 64) 16.1 -> 17.0. These are repeated calls. A first call on
+  // K and V that were written just before may find their last part in the Infinity Cache, which the line
+  // leaves out of account: 171 MiB (B4 32/8, 11000 keys) 35.8 -> 38.8 us in a first call (35.1 and 35.3 when
+  // repeated one at a time), 256 MiB 57.7 -> 53.1 after copies into place but 59.7 -> 61.3 straight from the
+  // generator, 512 MiB 122.6 -> 101.0; after 512 MiB of other writes 73.6 -> 36.1, 110 -> 48.6, 153 -> 87.6.
   constexpr double kStreamBytes = 128.0 * (1 << 20);
   const bool stream_kv = p.n_cb == 1 && 2.0 * p.batch * p.hkv * p.sk * (DQK + DV) > kStreamBytes;
   return hipLaunchKernel(stream_kv ? reinterpret_cast<const void*>(&fa_decode_kernel<DQK, DV, true>)

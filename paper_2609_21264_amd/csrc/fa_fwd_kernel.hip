@@ -236,8 +236,9 @@ struct WorkMap {
 // Logical work items are ordered by chunk of key/value heads (head_chunk heads each, the first
 // head_chunked of the batch's heads in whole chunks; the short and key-parts instances have one chunk),
 // then heaviest query block first (causal), then batch, key/value head and member; each group of `group`
-// consecutive items (the workgroups of one key/value head at one query block) is placed on one XCD, and groups go to XCDs round-robin (`full` = the items in whole spans of
-// 8 groups; the rest keep their order). FAST divides through
+// consecutive items (the workgroups of one key/value head at one query block) is placed on one XCD, and
+// groups go to XCDs round-robin (`full` = the items in whole spans of 8 groups; the rest keep their order).
+// FAST divides through
 // the multiply-high constants, else with the compiler's division sequence (the long instance: there
 // the faster prologue measured no gain in time, and on the 128K workload it shifted the relative
 // start times of the workgroups that stream one K/V head through an XCD's L2 enough to double the L2
@@ -590,7 +591,7 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
   // 32*QB-row chunks of the block's rows, so that all heads of the workgroup share every K/V tile
   // and, when HW = NWAVES, every wave visits the same key tiles (no wave idles through the tiles of
   // a causal diagonal that its rows do not see).
-  // With key halves (KSPLIT = 2) the same applies within each wave set: wave w belongs to set
+  // With key parts (KSPLIT = 2 or 4) the same applies within each wave set: wave w belongs to set
   // w / RWAVES, which takes keys [kpart, kpart + WBN) of every tile, and to row chunk w % RWAVES.
   const int hw_log = (int)((wm.shifts >> 18) & 3u);
   const int kset = C::KSPLIT > 1 ? wave / C::RWAVES : 0, rwave = C::KSPLIT > 1 ? wave % C::RWAVES : wave;
@@ -632,7 +633,8 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
 #pragma unroll
     for (int ks = 0; ks < A::KS; ++ks) load_q<A::AG>(st.qf[qb][ks], qh + (size_t)row * DQK + ks * 16 + st.h * 8);
   }
-  // What comes from the argument block (not preloaded) is used only from here on.
+  // What comes from the argument block (not preloaded) is used only from here on, but for the chunks of
+  // heads in decode_workgroup (long instance: see the entry kernels).
   const uint16_t* __restrict__ kh = p.k + (size_t)(b * p.hkv + g) * p.sk * DQK;
   const uint16_t* __restrict__ vh = p.v + (size_t)(b * p.hkv + g) * p.sk * DV;
   st.kg = kh;
@@ -974,15 +976,17 @@ __device__ __forceinline__ void fa_fwd_body(FwdParams p, const WorkMap wm) {
   }
 }
 
-// Entry kernels. The long instance reads everything from the argument block. The instances with
-// several workgroups per CU (short and key halves), whose workgroups are short chains on which the
-// first loads' latency is felt, take the values their prologue needs first as leading scalar
-// arguments, which the command processor preloads into SGPRs before the first instruction
+// Entry kernels. The instances with one workgroup per CU (long at d = 128 and 192, key quarters at d = 128)
+// read everything from the argument block. Those with several workgroups per CU, whose workgroups are
+// mostly short chains on which the first loads' latency is felt, take the values their prologue needs first
+// as leading scalar arguments, which the command processor preloads into SGPRs before the first instruction
 // (kernel-argument preloading, enabled at build time for the first 14 SGPRs of a kernel's leading
 // scalar arguments), and issue their Q loads before they read the argument block. Preloading is kept
-// off the long instance: it slows the launch of each wave, and on the 128K
+// off the long instance at d = 128: it slows the launch of each wave, and on the 128K
 // workload the spread-out starts of the workgroups that stream one K/V head through an XCD's L2
-// doubled the L2 misses, at no gain in time.
+// doubled the L2 misses, at no gain in time. At d = 64 the long instance takes it for having two workgroups
+// per CU, though its work order reads the chunks of heads from the argument block before the Q loads:
+// preloaded or not measured level (26 shapes of 1 025 to 4 000 blocks, 0.98-1.01x, mean 1.00x).
 template <class C>
 __global__ __attribute__((amdgpu_flat_work_group_size(C::NT, C::NT), amdgpu_waves_per_eu(C::WPE, C::WPE)))
 void fa_fwd_kernel(FwdParams p) {
@@ -1007,7 +1011,7 @@ void fa_fwd_kernel_preload(const uint16_t* a_q, int a_sq, int a_sk, int a_hq, in
 }
 
 // The instances. Long: 4 waves x 64 query rows (256 row-heads per workgroup), one workgroup per CU,
-// one wave per SIMD; the register budget of a wave (O 128 + Q 64 AGPRs at d = 128, two score tiles
+// one wave per SIMD (at d = 64 two, in 32-key tiles: Instance<64, 64> below); the register budget of a wave (O 128 + Q 64 AGPRs at d = 128, two score tiles
 // and P in VGPRs) is what fixes 64 query rows per wave. K tiles are loaded two ahead: a third K slot
 // measured 2-3 % slower on the 8K, 4K-d192 and 128K prefill shapes (one box, interleaved).
 // Short: 4 waves x 32 query rows (128 row-heads per workgroup), two workgroups per CU (two waves per SIMD,
@@ -1117,17 +1121,23 @@ bool key_quarters(const FwdParams& p, int d_qk, bool causal) {
 }
 
 // Largest grid of long-instance blocks (256 row-heads) that runs the short instance instead. At
-// d = 128 the CU count of MI355X, where the long instance would leave CUs idle. At d = 64, where a
-// step carries twice the softmax work per MFMA and the long instance's one wave per SIMD exposes it,
-// the short instance's two waves per SIMD pay off up to four blocks per CU: measured 5-17 % faster on
-// causal and non-causal GPT-2-shaped problems of 384-768 blocks, level at 1024-1152, 3-4 % slower from
-// 1536 blocks on (one box, interleaved).
+// d = 128 the CU count of MI355X, where the long instance would leave CUs idle. At d = 64 the line comes
+// from the long instance's earlier form with one wave per SIMD (short 5-17 % faster at 384-768 blocks, level
+// at 1024-1152). Against its present form (32-key tiles, two waves per SIMD; 110 random shapes, causal and
+// not, interleaved) the short instance takes 0.51-0.99 of the long one's time up to 512 blocks (five shapes
+// 1.02-1.08). From there it is a matter of padding: 0.52-0.97 up to 1024 where the long blocks pad over 1.05
+// times the short ones' rows, else 0.86-1.07 up to 704 blocks and 0.88-1.21 from 768 on (13 of 20 shapes
+// above 1.01; 16 heads B5 3031 x 3031 207 us against 188), and above 1024 likewise 0.53-1.11 and 0.78-1.15.
+// So a count of blocks fits neither side alone; 1024 lies where equal padding has mostly turned.
 constexpr int64_t kShortMaxBlocks64 = 1024, kShortMaxBlocks128 = 256;
 // Largest grid of such blocks that runs the key-halves instance, by head dimension and masking.
 // Causal problems have a longest chain of steps (the last query block's) that halving each step's
 // work per wave shortens; problems without a mask gain only while the grid leaves SIMDs idle. At
 // d = 128 causal grids of 256 blocks measured 0.96-1.06x against the short instance (the paper's
-// Llama S = 2048 shapes on the slow side), so they stay with it.
+// Llama S = 2048 shapes on the slow side), so they stay with it. Measured again with the merge by all wave
+// sets (88 random shapes around the four lines): below them the short instance takes 1.0-1.3 times the
+// halves' time, but for short sequences at the line itself (0.76-0.95: 24/12 heads B8 165 x 165), above them
+// 0.84-1.06 (0.86-1.25 at d = 64).
 constexpr int64_t kHalfMaxCausal64 = 320, kHalfMaxFull64 = 64, kHalfMaxCausal128 = 192, kHalfMaxFull128 = 128;
 
 enum class Kind { kLong, kShort, kShortWide, kHalf, kQuarter };
@@ -1233,6 +1243,7 @@ hipError_t launch_cfg(FwdParams p, hipStream_t stream) {
   // the light blocks of several heads still fill the end of the grid. Measured (interleaved, one box):
   // H128 S4096 192/128 causal 647 -> 615 us (chunks of 32 heads; 16: 629, 8: 644), without a mask
   // 1181 -> 1060, B4 H32 S4096 d128 causal 525 -> 510, without 923 -> 875, B16 H32 S512 91.7 -> 88.1.
+  // (The smaller chunks' times hold their smaller last chunk too, whose heads then fill less of the end.)
   // Fewer than four chunks stay in one: H16 S32768 d64 causal measured 1.4 % slower in two.
   p.head_chunk = p.batch * p.hkv;
   p.head_chunked = 0;
@@ -1418,7 +1429,8 @@ int launch_instance_id(int batch, int hq, int hkv, int sq, int sk, int d_qk, int
 }
 
 int64_t forward_workgroups(int batch, int hq, int hkv, int sq) {
-  // the long instance's grid (the other instances run only grids of at most 2 048 workgroups)
+  // the long instance's grid (the other instances of the fused forward run at most 2 048 workgroups; split
+  // mode's short one checks its own)
   using C = Instance<64, 64, false>::C;
   const int group = hq / hkv, hw_log = packed_heads_log2(group, C::RWAVES);
   const int64_t bmr = (C::NWAVES >> hw_log) * 32 * C::QB;

@@ -12,13 +12,12 @@
 // 2 * (d_qk + d_v) flops: the whole path's intensity is below d / 2 flop per byte (Sec. "The
 // Operational Intensity Constraint", Table 3), under MI355X's ridge point for any head dimension
 // here, so every kernel is written to stream HBM:
-//  * scores: one workgroup per block of 128 query rows, four waves that compute and one that loads K. The block's Q rows stay in registers as the
-//    B operand of S^T = K Q^T (v_mfma_f32_32x32x16_bf16); 64-key K tiles go HBM/L2 -> LDS through
-//    the direct-to-LDS buffer loads of the fused kernel, two tiles ahead in a three-slot ring (one
-//    tile ahead in two slots for d_qk = 192). With
-//    the K rows in the permuted order perm32, each lane's accumulator holds 8 consecutive keys of
-//    one query row per register group; the tile is staged through LDS so that every store writes
-//    whole 128-byte row segments.
+//  * scores: one workgroup per block of 128 query rows, four waves that compute and one that loads K. The
+//    block's Q rows stay in registers as the B operand of S^T = K Q^T (v_mfma_f32_32x32x16_bf16); 64-key K
+//    tiles go HBM/L2 -> LDS through the direct-to-LDS buffer loads of the fused kernel, two tiles ahead in a
+//    three-slot ring (one tile ahead in two slots for d_qk = 192). With the K rows in the permuted order
+//    perm32, each lane's accumulator holds 8 consecutive keys of one query row per register group; the tile
+//    is staged through LDS so that every store writes whole 128-byte row segments.
 //  * softmax: one wavefront per row, 16-byte loads and stores (1 KiB contiguous per instruction), in
 //    instances for rows of up to 512, 1024, .., 8192 keys that stay in registers between the statistics
 //    and the write; longer rows are read twice.
@@ -109,8 +108,14 @@ __device__ __forceinline__ void block_barrier() {
 //  * STREAM (see streams()): S is stored non-temporally, so that it
 //    does not push its own earlier lines through the cache, and the workgroups start their key sweeps at
 //    different tiles: in step, all of them write the same key columns of rows a power of two apart.
-//    32 heads S4096 d128: causal 175 -> 134 us (537 MB, 4.0 TB/s), full 320 -> 246 us (4.4 TB/s); the
-//    non-temporal stores alone 148 and 270, the sweeps alone 195 and 297, neither 212 and 454.
+//    The operator by itself, again and again over one buffer, 32 heads S4096 d128: causal 175 -> 134 us (537
+//    MB, 4.0 TB/s), full 320 -> 246 us (4.4 TB/s); the non-temporal stores alone 148 and 270, the sweeps
+//    alone 195 and 297, neither 212 and 454. Inside a whole call the operator takes longer for it, 165 ->
+//    191 us causal (2.8 TB/s): the caches hold what P V read last, and its stores reach HBM at once. What it
+//    saves is in the operators that follow, which find the caches free of S (softmax 252 -> 201 us, P V 157
+//    -> 125). The whole call, causal: 480 us; with S stored through the caches 514, with the sweeps in step
+//    488, with staggered sweeps but cached stores 517 (full 834, 1012, 903 and 890; 24 heads S2048 full 178,
+//    205, 199 and 175).
 constexpr int kScoreThreads = (kWaves + 1) * 64;
 
 // Tile (of nt > 0) at which block qb of head bh starts its staggered key sweep. Unsigned: bh goes up to the
