@@ -60,13 +60,28 @@ def test_split_config1_full():
     check_split(W.CONFIGS[1], 4)
 
 
-def test_split_one_part_equals_single_pass_bitwise():
-    # one part: O = bf16(acc / l) and LSE = m + ln l through the workspace, the same values as the
-    # single-pass kernel
-    w = W.small("one part", dqk=128, dv=128, Hq=4, Hkv=2, Sq=200, Sk=300, causal=True, seed=55)
-    q, k, v = W.make_inputs(w)
-    _, _, _, o1, l1 = run_split(w, 1, (q, k, v))
-    o2, l2 = fa.forward(q.cuda(), k.cuda(), v.cuda(), causal=True, scale=w.scale, return_lse=True)
+# (d_qk, d_v, Hq, Hkv, Sq, Sk, instance): sizes at which the single pass and one part of split mode run the same
+# instance in the same key tiles (the key parts, and the long instance at d = 64, have no such twin)
+ONE_PART = [(128, 128, 200, 50, 100, 150, fa.FA_INSTANCE_SHORT), (64, 64, 330, 110, 100, 150, fa.FA_INSTANCE_SHORT),
+            (128, 128, 264, 66, 250, 300, fa.FA_INSTANCE_LONG), (192, 128, 3, 3, 200, 300, fa.FA_INSTANCE_LONG)]
+
+
+@pytest.mark.parametrize("dqk,dv,hq,hkv,sq,sk,instance", ONE_PART)
+def test_split_one_part_equals_single_pass_bitwise(dqk, dv, hq, hkv, sq, sk, instance):
+    # one part: O = bf16(acc / l) and LSE = m + ln l through the workspace, the same values as the single
+    # pass (the wrapper runs the single pass for one part, so the entry point is called itself)
+    for parts in (0, 1):
+        assert fa.fa_fwd_instance(1, hq, hkv, sq, sk, dqk, dv, True, parts) == instance
+    w = W.small("one part", dqk=dqk, dv=dv, Hq=hq, Hkv=hkv, Sq=sq, Sk=sk, causal=True, seed=55)
+    q, k, v = (x.cuda() for x in W.make_inputs(w))
+    o2, l2 = fa.forward(q, k, v, causal=True, scale=w.scale, return_lse=True)
+    o1, l1 = torch.empty_like(o2), torch.empty_like(l2)
+    nbytes = fa.fa_fwd_split_workspace_bytes(1, hq, sq, dv, 1)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    st = fa.fa_fwd_split(q.data_ptr(), k.data_ptr(), v.data_ptr(), o1.data_ptr(), l1.data_ptr(), 1, hq, hkv, sq, sk,
+                         dqk, dv, w.scale, True, 1, ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+    assert st == fa.FA_OK
+    torch.cuda.synchronize()
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
 
 
